@@ -10,20 +10,32 @@
 // stable sort, on (capacity - degree, row), gives the rows by descending
 // degree with ties in ascending row id.
 //
-// Radix pass: 8-bit digits, 4,096 keys per workgroup.  Each wavefront ranks
-// its 1,024 keys in 16 steps of 64: lanes with equal digits find each other
-// with eight ballots, take their rank within the step from a popcount, and
-// read the running count of their digit from the wavefront's LDS counters.
-// Counts of all workgroups are scanned digit-major, so equal digits keep
-// their input order across workgroups as well.
+// Radix pass: digits of up to 9 bits, the passes of a sort sharing its bits
+// evenly (18-bit row ids take two passes), 8,192 keys per workgroup.  Each
+// wavefront ranks its 1,024 keys in 16 steps of 64: lanes with equal digits
+// find each other with one ballot per digit bit, take their rank within the
+// step from a popcount, and read the running count of their digit from the
+// wavefront's LDS counters.  Counts of all workgroups are scanned
+// digit-major, so equal digits keep their input order across workgroups as
+// well.  A workgroup puts its keys, and then each array of values, in digit
+// order in LDS before it stores them, so that the stores of a wavefront
+// cover runs of consecutive addresses (16 keys of a digit on average at 9
+// bits) rather than 64 lines: the pass is bound by its reads and writes of
+// memory.  Two arrays of values can travel with the keys (an edge's id and
+// its other endpoint), which leaves no random gather of endpoints after the
+// sort.
 #include "device.h"
 
 namespace gnnk {
 namespace {
 
-constexpr int RS_WAVES = 4;
+constexpr int RS_WAVES = 8;
+constexpr int RS_BLOCK = RS_WAVES * 64;
 constexpr int RS_STEPS = 16;                       // 64-key steps per wavefront
 constexpr int RS_TILE = RS_WAVES * 64 * RS_STEPS;  // keys per workgroup
+constexpr int RS_BITS = 9;                         // most bits of a digit
+constexpr int RS_DIGITS = 1 << RS_BITS;
+static_assert(RS_DIGITS == RS_BLOCK, "thread d of a workgroup handles digit d");
 constexpr int SCAN_ITEMS = 16;
 constexpr int SCAN_TILE = 256 * SCAN_ITEMS;
 
@@ -38,58 +50,95 @@ inline unsigned grid_1d(int64_t n) {
 // ---------------------------------------------------------------------------
 // radix sort
 
-__global__ __launch_bounds__(256) void rs_count_kernel(const uint32_t* keys, int64_t n, int shift, uint32_t* hist,
-                                                       int64_t n_tiles) {
-    __shared__ uint32_t c[256];
+__global__ __launch_bounds__(RS_BLOCK) void rs_count_kernel(const uint32_t* keys, int64_t n, int shift, int bits,
+                                                            uint32_t* hist, int64_t n_tiles) {
+    __shared__ uint32_t c[RS_DIGITS];
+    const uint32_t mask = (1u << bits) - 1u;
     c[threadIdx.x] = 0u;
     __syncthreads();
     const int64_t base = (int64_t)blockIdx.x * RS_TILE;
-    for (int j = 0; j < RS_TILE / 256; ++j) {
-        const int64_t i = base + j * 256 + threadIdx.x;
-        if (i < n) atomicAdd(&c[(keys[i] >> shift) & 255u], 1u);
+#pragma unroll
+    for (int j = 0; j < RS_STEPS; ++j) {
+        const int64_t i = base + j * RS_BLOCK + threadIdx.x;
+        if (i < n) atomicAdd(&c[(keys[i] >> shift) & mask], 1u);
     }
     __syncthreads();
-    hist[(int64_t)threadIdx.x * n_tiles + blockIdx.x] = c[threadIdx.x];
+    if (threadIdx.x <= mask) hist[(int64_t)threadIdx.x * n_tiles + blockIdx.x] = c[threadIdx.x];
+}
+
+// exclusive prefix of v over the threads of the workgroup
+__device__ uint32_t rs_exclusive(uint32_t v, uint32_t* wsum) {
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    uint32_t inc = v;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t t = __shfl_up(inc, o, 64);
+        if (lane >= o) inc += t;
+    }
+    if (lane == 63) wsum[w] = inc;
+    __syncthreads();
+    uint32_t off = 0u;
+#pragma unroll
+    for (int i = 0; i < RS_WAVES; ++i) off += i < w ? wsum[i] : 0u;
+    return off + inc - v;
 }
 
 // hist holds the exclusive digit-major scan of the counts: the first output
-// position of (digit, workgroup)
-__global__ __launch_bounds__(256) void rs_scatter_kernel(const uint32_t* keys, const uint32_t* vals, int64_t n,
-                                                         int shift, const uint32_t* hist, int64_t n_tiles,
-                                                         uint32_t* keys_out, uint32_t* vals_out) {
-    __shared__ uint32_t cnt[RS_WAVES][256];
+// position of (digit, workgroup).  NV: arrays of values that move with the
+// keys (v0 == nullptr stands for 0..n-1).  keys_out == nullptr drops the
+// sorted keys.
+template <int NV>
+__global__ __launch_bounds__(RS_BLOCK) void rs_scatter_kernel(const uint32_t* keys, const uint32_t* v0,
+                                                              const uint32_t* v1, int64_t n, int shift, int bits,
+                                                              const uint32_t* hist, int64_t n_tiles,
+                                                              uint32_t* keys_out, uint32_t* out0, uint32_t* out1) {
+    __shared__ uint32_t cnt[RS_WAVES][RS_DIGITS];
+    __shared__ uint32_t first[RS_DIGITS];  // output position of a digit's first key less its place in the tile
+    __shared__ uint32_t wsum[RS_WAVES];
+    __shared__ uint32_t stage[RS_TILE];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    for (int i = threadIdx.x; i < RS_WAVES * 256; i += 256) (&cnt[0][0])[i] = 0u;
+    const uint32_t mask = (1u << bits) - 1u;
+    for (int i = threadIdx.x; i < RS_WAVES * RS_DIGITS; i += RS_BLOCK) (&cnt[0][0])[i] = 0u;
     __syncthreads();
-    const int64_t base = (int64_t)blockIdx.x * RS_TILE + (int64_t)w * (64 * RS_STEPS);
+    const int64_t tile = (int64_t)blockIdx.x * RS_TILE;
+    const int64_t base = tile + (int64_t)w * (64 * RS_STEPS);
+    const int m = (int)(n - tile < RS_TILE ? n - tile : RS_TILE);  // keys of this tile
     const uint64_t below = lane ? (~0ull >> (64 - lane)) : 0ull;
-    uint32_t k[RS_STEPS], v[RS_STEPS], rank[RS_STEPS];
+    uint32_t k[RS_STEPS], a[RS_STEPS], b[RS_STEPS], at[RS_STEPS];
 #pragma unroll
     for (int j = 0; j < RS_STEPS; ++j) {
         const int64_t i = base + j * 64 + lane;
         const bool ok = i < n;
         k[j] = ok ? keys[i] : 0u;
-        v[j] = ok ? (vals ? vals[i] : (uint32_t)i) : 0u;
-        const uint32_t d = (k[j] >> shift) & 255u;
-        uint64_t peers = __ballot(ok);
+        a[j] = ok ? (v0 ? v0[i] : (uint32_t)i) : 0u;
+        b[j] = NV > 1 && ok ? v1[i] : 0u;
+    }
 #pragma unroll
-        for (int b = 0; b < 8; ++b) {
-            const uint64_t m = __ballot((d >> b) & 1u);
-            peers &= ((d >> b) & 1u) ? m : ~m;
+    for (int j = 0; j < RS_STEPS; ++j) {
+        const bool ok = base + j * 64 + lane < n;
+        const uint32_t d = (k[j] >> shift) & mask;
+        uint64_t peers = __ballot(ok);
+        for (int t = 0; t < bits; ++t) {
+            const uint64_t bm = __ballot((d >> t) & 1u);
+            peers &= ((d >> t) & 1u) ? bm : ~bm;
         }
         // every lane reads its digit's count before the last lane of each
         // digit group advances it (one LDS read, then one LDS write, in the
         // wavefront's program order)
         const uint32_t start = cnt[w][d];
-        rank[j] = start + (uint32_t)__popcll(peers & below);
+        at[j] = start + (uint32_t)__popcll(peers & below);
         __builtin_amdgcn_wave_barrier();
         if (ok && (peers >> lane) == 1ull) cnt[w][d] = start + (uint32_t)__popcll(peers);
         __builtin_amdgcn_wave_barrier();
     }
     __syncthreads();
     {
-        const int d = threadIdx.x;
-        uint32_t run = hist[(int64_t)d * n_tiles + blockIdx.x];
+        const uint32_t d = threadIdx.x;
+        uint32_t tot = 0u;
+#pragma unroll
+        for (int ww = 0; ww < RS_WAVES; ++ww) tot += cnt[ww][d];
+        uint32_t run = rs_exclusive(tot, wsum);
+        first[d] = (d <= mask ? hist[(int64_t)d * n_tiles + blockIdx.x] : 0u) - run;
 #pragma unroll
         for (int ww = 0; ww < RS_WAVES; ++ww) {
             const uint32_t c = cnt[ww][d];
@@ -98,22 +147,49 @@ __global__ __launch_bounds__(256) void rs_scatter_kernel(const uint32_t* keys, c
         }
     }
     __syncthreads();
+    // the keys in digit order; at becomes a key's place in the tile, and `to`
+    // the output position of the keys this thread stores
 #pragma unroll
     for (int j = 0; j < RS_STEPS; ++j) {
-        const int64_t i = base + j * 64 + lane;
-        if (i < n) {
-            const uint32_t p = cnt[w][(k[j] >> shift) & 255u] + rank[j];
-            keys_out[p] = k[j];
-            vals_out[p] = v[j];
+        if (base + j * 64 + lane < n) {
+            at[j] += cnt[w][(k[j] >> shift) & mask];
+            stage[at[j]] = k[j];
         }
     }
+    __syncthreads();
+    uint32_t to[RS_STEPS];
+#pragma unroll
+    for (int j = 0; j < RS_STEPS; ++j) {
+        const int i = j * RS_BLOCK + (int)threadIdx.x;
+        to[j] = 0u;
+        if (i < m) {
+            const uint32_t key = stage[i];
+            to[j] = first[(key >> shift) & mask] + (uint32_t)i;
+            if (keys_out) keys_out[to[j]] = key;
+        }
+    }
+    auto put = [&](const uint32_t* v, uint32_t* out) {
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < RS_STEPS; ++j)
+            if (base + j * 64 + lane < n) stage[at[j]] = v[j];
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < RS_STEPS; ++j) {
+            const int i = j * RS_BLOCK + (int)threadIdx.x;
+            if (i < m) out[to[j]] = stage[i];
+        }
+    };
+    put(a, out0);
+    if constexpr (NV > 1) put(b, out1);
 }
 
-__global__ void copy_pairs_kernel(const uint32_t* keys, const uint32_t* vals, int64_t n, uint32_t* keys_out,
-                                  uint32_t* vals_out) {
+__global__ void copy_pairs_kernel(const uint32_t* keys, const uint32_t* v0, const uint32_t* v1, int64_t n,
+                                  uint32_t* keys_out, uint32_t* out0, uint32_t* out1) {
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-        keys_out[i] = keys[i];
-        vals_out[i] = vals ? vals[i] : (uint32_t)i;
+        if (keys_out) keys_out[i] = keys[i];
+        out0[i] = v0 ? v0[i] : (uint32_t)i;
+        if (v1) out1[i] = v1[i];
     }
 }
 
@@ -209,14 +285,16 @@ __global__ void degree_kernel(const P* ptr, int64_t n_rows, int32_t* deg, uint32
     }
 }
 
-__global__ void gather_kernel(const int32_t* table, const uint32_t* idx, int64_t n, int32_t* out) {
-    for (int64_t p = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; p < n; p += (int64_t)gridDim.x * blockDim.x)
-        out[p] = table[idx[p]];
-}
-
+// At most one atomic per wavefront that saw a difference, and none once the
+// flag is seen set: all of them meet at one address (one per difference took
+// about 20 ms for a shuffled list of 114.6M ids, one per wavefront 3 ms).
 __global__ void check_identity_kernel(const int32_t* eid, int64_t n, int32_t* flag, int32_t bit) {
+    bool off = false;
     for (int64_t p = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; p < n; p += (int64_t)gridDim.x * blockDim.x)
-        if (eid[p] != (int32_t)p) atomicOr(flag, bit);
+        off |= eid[p] != (int32_t)p;
+    const uint64_t m = __ballot(off);
+    if (m == 0ull || (threadIdx.x & 63) != (unsigned)__builtin_ctzll(m)) return;
+    if (!(__hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & bit)) atomicOr(flag, bit);
 }
 
 __global__ void count_ids_kernel(const int32_t* eid, int64_t n, uint32_t* counts, int32_t* flag, int32_t bit) {
@@ -268,49 +346,58 @@ __global__ void hub_segments_kernel(const P* ptr, const int32_t* perm, const int
 int key_bits(uint64_t max_key) { return max_key == 0 ? 0 : 64 - __builtin_clzll(max_key); }
 
 size_t radix_scratch_words(int64_t n) {
-    const int64_t hist = 256 * (int64_t)tiles_of(n, RS_TILE);
+    const int64_t hist = RS_DIGITS * (int64_t)tiles_of(n, RS_TILE);
     return (size_t)(hist + tiles_of(hist, SCAN_TILE) + 64);
 }
 
 hipError_t scan_exclusive_u32(uint32_t* x, int64_t n, uint32_t* part, hipStream_t s) {
     if (n <= 0) return hipSuccess;
     const unsigned tiles = tiles_of(n, SCAN_TILE);
+    if (tiles <= 8) {
+        // few counts: one workgroup scans them (one launch instead of three)
+        hipLaunchKernelGGL(scan_carry_kernel, dim3(1), dim3(256), 0, s, x, n);
+        return hipGetLastError();
+    }
     hipLaunchKernelGGL(scan_reduce_kernel, dim3(tiles), dim3(256), 0, s, x, n, part);
     hipLaunchKernelGGL(scan_carry_kernel, dim3(1), dim3(256), 0, s, part, (int64_t)tiles);
     hipLaunchKernelGGL(scan_apply_kernel, dim3(tiles), dim3(256), 0, s, x, n, part);
     return hipGetLastError();
 }
 
-hipError_t radix_sort_pairs(const uint32_t* keys_in, const uint32_t* vals_in, int64_t n, int bits,
-                            uint32_t* keys_out, uint32_t* vals_out, uint32_t* tmp_keys, uint32_t* tmp_vals,
-                            uint32_t* scratch, hipStream_t s) {
+hipError_t radix_sort(const RadixArrays& in, const RadixArrays& out, const RadixArrays& tmp, int64_t n, int bits,
+                      uint32_t* scratch, hipStream_t s) {
     if (n <= 0) return hipSuccess;
-    const int passes = (bits + 7) / 8;
+    const int passes = (bits + RS_BITS - 1) / RS_BITS;
     if (passes == 0) {
-        hipLaunchKernelGGL(copy_pairs_kernel, dim3(grid_1d(n)), dim3(256), 0, s, keys_in, vals_in, n, keys_out,
-                           vals_out);
+        hipLaunchKernelGGL(copy_pairs_kernel, dim3(grid_1d(n)), dim3(256), 0, s, in.key, in.v0, in.v1, n, out.key,
+                           out.v0, out.v1);
         return hipGetLastError();
     }
     const int64_t n_tiles = tiles_of(n, RS_TILE);
     uint32_t* hist = scratch;
-    uint32_t* part = scratch + 256 * n_tiles;
-    const uint32_t* k_src = keys_in;
-    const uint32_t* v_src = vals_in;
+    uint32_t* part = scratch + RS_DIGITS * n_tiles;
+    RadixArrays src = in;
+    int shift = 0;
     for (int pass = 0; pass < passes; ++pass) {
-        // the last pass lands in the output buffers
-        const bool to_out = ((passes - 1 - pass) % 2) == 0;
-        uint32_t* k_dst = to_out ? keys_out : tmp_keys;
-        uint32_t* v_dst = to_out ? vals_out : tmp_vals;
-        const int shift = 8 * pass;
-        hipLaunchKernelGGL(rs_count_kernel, dim3((unsigned)n_tiles), dim3(256), 0, s, k_src, n, shift, hist, n_tiles);
-        hipError_t e = scan_exclusive_u32(hist, 256 * n_tiles, part, s);
+        // the passes share the bits evenly; the last one lands in the output
+        const int db = (bits - shift + passes - pass - 1) / (passes - pass);
+        const bool last = pass == passes - 1;
+        RadixArrays dst = ((passes - 1 - pass) % 2) == 0 ? out : tmp;
+        const dim3 grid((unsigned)n_tiles), block(RS_BLOCK);
+        hipLaunchKernelGGL(rs_count_kernel, grid, block, 0, s, src.key, n, shift, db, hist, n_tiles);
+        hipError_t e = scan_exclusive_u32(hist, ((int64_t)1 << db) * n_tiles, part, s);
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(rs_scatter_kernel, dim3((unsigned)n_tiles), dim3(256), 0, s, k_src, v_src, n, shift,
-                           hist, n_tiles, k_dst, v_dst);
+        uint32_t* keys_out = last ? out.key : dst.key;
+        if (in.v1)
+            hipLaunchKernelGGL(rs_scatter_kernel<2>, grid, block, 0, s, src.key, src.v0, src.v1, n, shift, db, hist,
+                               n_tiles, keys_out, dst.v0, dst.v1);
+        else
+            hipLaunchKernelGGL(rs_scatter_kernel<1>, grid, block, 0, s, src.key, src.v0, nullptr, n, shift, db, hist,
+                               n_tiles, keys_out, dst.v0, nullptr);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
-        k_src = k_dst;
-        v_src = v_dst;
+        src = dst;
+        shift += db;
     }
     return hipSuccess;
 }
@@ -333,12 +420,6 @@ hipError_t launch_degrees(const void* ptr, int ptr64, int64_t n_rows, int32_t* d
         hipLaunchKernelGGL(degree_kernel<int64_t>, grid, block, 0, s, (const int64_t*)ptr, n_rows, deg, deg_key, cap);
     else
         hipLaunchKernelGGL(degree_kernel<int32_t>, grid, block, 0, s, (const int32_t*)ptr, n_rows, deg, deg_key, cap);
-    return hipGetLastError();
-}
-
-hipError_t launch_gather(const int32_t* table, const uint32_t* idx, int64_t n, int32_t* out, hipStream_t s) {
-    if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(gather_kernel, dim3(grid_1d(n)), dim3(256), 0, s, table, idx, n, out);
     return hipGetLastError();
 }
 

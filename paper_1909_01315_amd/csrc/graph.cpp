@@ -151,6 +151,7 @@ constexpr int32_t FLAG_NOT_IDENT = 8; // edge ids differ from in-CSR positions
 struct Layout {
     size_t in_ptr = 0, in_idx = 0, in_eid = 0, out_ptr = 0, out_idx = 0, out_eid = 0;
     size_t in_deg = 0, out_deg = 0, in_perm = 0, out_perm = 0, in_row = 0, out_row = 0, out_pos = 0, flag = 0;
+    size_t tmp_a = 0, tmp_b = 0;   // E words each: temporaries of the reverse graph's sort
     size_t tmp = 0, tmp_words = 0;  // the build's temporaries (radix-sort counts, degree and segment sort keys)
     size_t in_hub = 0, out_hub = 0, in_seg = 0, out_seg = 0, in_sego = 0, out_sego = 0, total = 0;
     size_t fine_hub = 0, fine_seg = 0, fine_sego = 0;  // the reverse CSR's finer hub tables
@@ -205,6 +206,8 @@ Layout make_layout(int64_t n_src, int64_t n_dst, int64_t E, size_t ps, int64_t S
     L.in_row = b.take((size_t)E * 4);
     L.out_row = b.take((size_t)E * 4);
     L.out_pos = b.take((size_t)E * 4);
+    L.tmp_a = b.take((size_t)E * 4);
+    L.tmp_b = b.take((size_t)E * 4);
     L.flag = b.take(ALIGN);
     L.in_rowt = b.take((size_t)n_dst * 16);
     L.out_rowt = b.take((size_t)n_src * 16);
@@ -282,6 +285,14 @@ struct Builder {
         scratch_words = L.tmp_words;
     }
 
+    // edges sorted stably by `row_of_e`: out = {row, edge id, other endpoint} per position
+    void sort_edges(const int32_t* row_of_e, const int32_t* other_of_e, int bits, const RadixArrays& out,
+                    const RadixArrays& tmp) {
+        const RadixArrays in{const_cast<uint32_t*>(reinterpret_cast<const uint32_t*>(row_of_e)), nullptr,
+                             const_cast<uint32_t*>(reinterpret_cast<const uint32_t*>(other_of_e))};
+        chk(radix_sort(in, out, tmp, g->n_edges, bits, scratch, s));
+    }
+
     // the reverse graph's CSR from the source and destination of every edge id
     void build_reverse(const int32_t* src_of_e, const int32_t* dst_of_e) {
         const int64_t E = g->n_edges;
@@ -291,11 +302,10 @@ struct Builder {
         d.eid = at<int32_t>(L.out_eid);
         d.row = at<int32_t>(L.out_row);
         d.pos = at<int32_t>(L.out_pos);
-        chk(radix_sort_pairs(reinterpret_cast<const uint32_t*>(src_of_e), nullptr, E, row_bits(g->n_src),
-                             at<uint32_t>(L.out_row), at<uint32_t>(L.out_eid), at<uint32_t>(L.out_idx),
-                             at<uint32_t>(L.out_pos), scratch, s));
+        sort_edges(src_of_e, dst_of_e, row_bits(g->n_src), {at<uint32_t>(L.out_row), at<uint32_t>(L.out_eid),
+                                                            at<uint32_t>(L.out_idx)},
+                   {at<uint32_t>(L.out_pos), at<uint32_t>(L.tmp_a), at<uint32_t>(L.tmp_b)});
         chk(launch_ptr_from_keys(at<uint32_t>(L.out_row), E, g->n_src, W + L.out_ptr, g->ptr64, s));
-        chk(launch_gather(dst_of_e, at<uint32_t>(L.out_eid), E, at<int32_t>(L.out_idx), s));
         chk(launch_inverse(at<int32_t>(L.out_eid), E, at<int32_t>(L.out_pos), s));
     }
 
@@ -311,8 +321,8 @@ struct Builder {
         uint32_t* tv = tk + pad;
         uint32_t* rs = tv + pad;
         chk(launch_degrees(d.ptr, g->ptr64, n, d.deg, key, (uint32_t)E, s));
-        chk(radix_sort_pairs(key, nullptr, n, key_bits((uint64_t)E), sorted, reinterpret_cast<uint32_t*>(d.perm), tk,
-                             tv, rs, s));
+        chk(radix_sort({key, nullptr, nullptr}, {sorted, reinterpret_cast<uint32_t*>(d.perm), nullptr},
+                       {tk, tv, nullptr}, n, key_bits((uint64_t)E), rs, s));
         keys_h.resize((size_t)n);
         if (n > 0) chk(hipMemcpyAsync(keys_h.data(), sorted, (size_t)n * 4, hipMemcpyDeviceToHost, s));
     }
@@ -340,8 +350,8 @@ struct Builder {
         uint32_t* tv = tk + pad;
         uint32_t* rs = tv + pad;
         chk(launch_seg_keys(d.seg, n, d.idx, key, s));
-        chk(radix_sort_pairs(key, nullptr, n, key_bits(n_cols > 1 ? (uint64_t)(n_cols - 1) : 0), sorted,
-                             reinterpret_cast<uint32_t*>(d.seg_order), tk, tv, rs, s));
+        chk(radix_sort({key, nullptr, nullptr}, {sorted, reinterpret_cast<uint32_t*>(d.seg_order), nullptr},
+                       {tk, tv, nullptr}, n, row_bits(n_cols), rs, s));
     }
 
     // common tail: degree order, identity flag, hub tables
@@ -495,11 +505,10 @@ gnnk_status create_coo(Builder& b, const int32_t* src, const int32_t* dst, void*
     in.eid = b.at<int32_t>(L.in_eid);
     in.row = b.at<int32_t>(L.in_row);
     // in-CSR: edges sorted by destination, ties in edge-id order
-    b.chk(radix_sort_pairs(reinterpret_cast<const uint32_t*>(dst), nullptr, E, row_bits(g->n_dst),
-                           b.at<uint32_t>(L.in_row), b.at<uint32_t>(L.in_eid), b.at<uint32_t>(L.out_row),
-                           b.at<uint32_t>(L.out_pos), b.scratch, b.s));
+    b.sort_edges(dst, src, row_bits(g->n_dst), {b.at<uint32_t>(L.in_row), b.at<uint32_t>(L.in_eid),
+                                                b.at<uint32_t>(L.in_idx)},
+                 {b.at<uint32_t>(L.out_row), b.at<uint32_t>(L.out_eid), b.at<uint32_t>(L.out_idx)});
     b.chk(launch_ptr_from_keys(b.at<uint32_t>(L.in_row), E, g->n_dst, b.W + L.in_ptr, g->ptr64, b.s));
-    b.chk(launch_gather(src, b.at<uint32_t>(L.in_eid), E, b.at<int32_t>(L.in_idx), b.s));
     b.chk(launch_check_identity(b.at<int32_t>(L.in_eid), E, g->flag, FLAG_NOT_IDENT, b.s));
     b.build_reverse(src, dst);
     return b.finish(ws_bytes, true);

@@ -269,23 +269,27 @@ hipError_t launch_row_table(const void* ptr, int ptr64, const int32_t* perm, int
                             hipStream_t s);
 // bits needed for keys in [0, max_key]
 int key_bits(uint64_t max_key);
-// uint32 words of scratch radix_sort_pairs needs for n pairs
+// uint32 words of scratch radix_sort needs for n keys
 size_t radix_scratch_words(int64_t n);
-// Stable sort of (key, value) pairs by the low `bits` bits of the key; vals_in
-// == nullptr stands for 0..n-1.  Inputs are only read; the result lands in
-// keys_out/vals_out; tmp_keys/tmp_vals (n entries each) and scratch are
-// clobbered.  No buffer may alias another.
-hipError_t radix_sort_pairs(const uint32_t* keys_in, const uint32_t* vals_in, int64_t n, int bits,
-                            uint32_t* keys_out, uint32_t* vals_out, uint32_t* tmp_keys, uint32_t* tmp_vals,
-                            uint32_t* scratch, hipStream_t s);
+// keys and the one or two arrays of values that move with them
+struct RadixArrays {
+    uint32_t* key;
+    uint32_t* v0;
+    uint32_t* v1;  // nullptr: one array of values
+};
+// Stable sort of n keys and their values by the low `bits` bits of the key.
+// in is only read (in.v0 == nullptr stands for 0..n-1); the result lands in
+// out, whose key may be nullptr where bits needs at most two passes; tmp (n
+// entries each, used from two passes on) and scratch are clobbered.  No
+// array may alias another.
+hipError_t radix_sort(const RadixArrays& in, const RadixArrays& out, const RadixArrays& tmp, int64_t n, int bits,
+                      uint32_t* scratch, hipStream_t s);
 // ptr[r] = first position of the sorted keys that is >= r, r in [0, n_rows]
 hipError_t launch_ptr_from_keys(const uint32_t* keys, int64_t n_keys, int64_t n_rows, void* ptr, int ptr64,
                                 hipStream_t s);
 // deg[r] = ptr[r + 1] - ptr[r]; deg_key[r] = cap - deg[r]
 hipError_t launch_degrees(const void* ptr, int ptr64, int64_t n_rows, int32_t* deg, uint32_t* deg_key, uint32_t cap,
                           hipStream_t s);
-// out[p] = table[idx[p]]
-hipError_t launch_gather(const int32_t* table, const uint32_t* idx, int64_t n, int32_t* out, hipStream_t s);
 // flag |= bit unless eid[p] == p for every p
 hipError_t launch_check_identity(const int32_t* eid, int64_t n, int32_t* flag, int32_t bit, hipStream_t s);
 // flag |= bit unless eid is a permutation of 0..n-1 (counts: n words of scratch)
