@@ -134,10 +134,11 @@ typedef struct {
  * ascending order (an edge list sorted by destination, then source) the
  * segments processed at the same time gather from one slice of the neighbour
  * table.  The order never changes a result: segment partials are combined in
- * table order.
- * The call synchronises `stream` twice (after checking the input, and to read
- * back the sorted degrees); it allocates no device memory (its temporaries
- * are part of the workspace). */
+ * table order (graphs of fewer than 2^20 edges keep table order).
+ * The call synchronises `stream` once, to read back the input check and what
+ * the schedules need of the sorted degrees, and graph_create_csr once more
+ * before it, to refuse row offsets that cannot be walked; it allocates no
+ * device memory (its temporaries are part of the workspace). */
 
 /* Upper bound of the workspace for a graph of this size; ptr_t is the width
  * of the CSR row offsets the handle builds (either width for any size).

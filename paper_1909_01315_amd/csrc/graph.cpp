@@ -4,13 +4,13 @@
 //
 // Every structure is built on the device (build.hip: stable radix sorts, so
 // the edges of a node keep ascending edge id) into the caller's workspace.
-// The host reads back only a flag word and the sorted degrees, from which it
-// derives the role boundaries of the schedule and the hub segment offsets.
+// The host reads back only a summary (a flag word, and how many rows are
+// longer than each threshold a schedule can ask for), which places the role
+// boundaries of the schedules and sizes the hub tables.
 #include <stdio.h>
 #include <string.h>
 
 #include <algorithm>
-#include <numeric>
 
 #include "host.h"
 
@@ -71,11 +71,11 @@ int64_t seg_edges_fine_for(int64_t E) {
 }
 
 int64_t Dir::count_above(int64_t t) const {
-    // sorted_deg is descending: the first position whose degree is <= t is the
-    // first x with t >= x
-    auto it = std::upper_bound(sorted_deg.begin(), sorted_deg.end(), (int32_t)std::min<int64_t>(t, INT32_MAX),
-                               [](int32_t v, int32_t x) { return v >= x; });
-    return (int64_t)(it - sorted_deg.begin());
+    if (t < 0) return n_rows;
+    // every threshold a call uses is at most SUMMARY_DEG (the small-row
+    // option's limit), or the table's own segment size or far_deg
+    if (t > SUMMARY_DEG) return t == far_deg ? n_far : n_hub;
+    return above.empty() ? 0 : above[(size_t)t];
 }
 
 void* Scratch::take(size_t n) {
@@ -151,8 +151,8 @@ constexpr int32_t FLAG_NOT_IDENT = 8; // edge ids differ from in-CSR positions
 struct Layout {
     size_t in_ptr = 0, in_idx = 0, in_eid = 0, out_ptr = 0, out_idx = 0, out_eid = 0;
     size_t in_deg = 0, out_deg = 0, in_perm = 0, out_perm = 0, in_row = 0, out_row = 0, out_pos = 0, flag = 0;
-    size_t tmp_a = 0, tmp_b = 0;   // E words each: temporaries of the reverse graph's sort
-    size_t tmp = 0, tmp_words = 0;  // the build's temporaries (radix-sort counts, degree and segment sort keys)
+    size_t edge_tmp[5] = {};        // E words each: temporaries of the sorts
+    size_t tmp = 0, tmp_words = 0;  // the build's temporaries (radix-sort counts, degree sort keys)
     size_t in_hub = 0, out_hub = 0, in_seg = 0, out_seg = 0, in_sego = 0, out_sego = 0, total = 0;
     size_t fine_hub = 0, fine_seg = 0, fine_sego = 0;  // the reverse CSR's finer hub tables
     size_t in_rowt = 0, out_rowt = 0, in_segw = 0, out_segw = 0, fine_segw = 0;  // per-wavefront lookup tables
@@ -172,24 +172,20 @@ struct Bump {
 // most E / S of them, and at most E / S + (hub rows) <= 2 E / S + 2 segments
 int64_t max_segments(int64_t E, int64_t S) { return 2 * E / S + 2; }
 
-// the smallest segment size of a graph's tables (the most segments)
-int64_t min_seg_edges(const gnnk_graph* g) {
-    return std::min({g->seg_edges, g->seg_edges_out, g->seg_edges_fine, g->seg_edges_in_fine});
+size_t pad64(int64_t x) { return (size_t)((x + 63) / 64 * 64); }
+
+// uint32 words of build temporaries beside the edge-sized ones: the counts of
+// the edge sorts, or four arrays of both directions' rows and the counts of
+// their degree sorts, or the counts of the segment sort (at most E / 4
+// segments: 2 E / S + 2 in each of four tables, S >= 32, none below 33 edges)
+size_t build_tmp_words(int64_t n_src, int64_t n_dst, int64_t E) {
+    return std::max({radix_scratch_words(E, E),
+                     4 * (pad64(n_src) + pad64(n_dst)) + radix_scratch_words(n_dst, n_src),
+                     radix_scratch_words(E / 4 + 64, 0)});
 }
 
-// uint32 words of build temporaries: the radix sort of the edges, or four
-// row-sized arrays plus the sort of the degree keys, or the same for the
-// segment keys
-size_t build_tmp_words(int64_t n_src, int64_t n_dst, int64_t E, int64_t S) {
-    const int64_t n = std::max(n_src, n_dst);
-    const int64_t m = max_segments(E, S);
-    auto pad = [](int64_t x) { return (size_t)((x + 63) / 64 * 64); };
-    return std::max({radix_scratch_words(E), 4 * pad(n + 64) + radix_scratch_words(n),
-                     4 * pad(m) + radix_scratch_words(m)});
-}
-
-Layout make_layout(int64_t n_src, int64_t n_dst, int64_t E, size_t ps, int64_t S, int64_t hub_in, int64_t hub_out,
-                   int64_t seg_in, int64_t seg_out, int64_t hub_fine = 0, int64_t seg_fine = 0,
+Layout make_layout(int64_t n_src, int64_t n_dst, int64_t E, size_t ps, int64_t hub_in, int64_t hub_out, int64_t seg_in,
+                   int64_t seg_out, int64_t hub_fine = 0, int64_t seg_fine = 0,
                    int64_t hub_ifine = 0, int64_t seg_ifine = 0) {
     Layout L;
     Bump b;
@@ -206,12 +202,11 @@ Layout make_layout(int64_t n_src, int64_t n_dst, int64_t E, size_t ps, int64_t S
     L.in_row = b.take((size_t)E * 4);
     L.out_row = b.take((size_t)E * 4);
     L.out_pos = b.take((size_t)E * 4);
-    L.tmp_a = b.take((size_t)E * 4);
-    L.tmp_b = b.take((size_t)E * 4);
-    L.flag = b.take(ALIGN);
+    for (size_t& o : L.edge_tmp) o = b.take((size_t)E * 4);
+    L.flag = b.take(sizeof(BuildSummary));
     L.in_rowt = b.take((size_t)n_dst * 16);
     L.out_rowt = b.take((size_t)n_src * 16);
-    L.tmp_words = build_tmp_words(n_src, n_dst, E, S);
+    L.tmp_words = build_tmp_words(n_src, n_dst, E);
     L.tmp = b.take(L.tmp_words * 4);
     L.in_hub = b.take((size_t)(hub_in + 1) * 4);
     L.out_hub = b.take((size_t)(hub_out + 1) * 4);
@@ -242,19 +237,17 @@ bool sizes_ok(int64_t n_src, int64_t n_dst, int64_t E) {
     return n_src >= 0 && n_dst >= 0 && E >= 0 && n_src < INT32_MAX && n_dst < INT32_MAX && E <= MAX_EDGES;
 }
 
+// edges from which the segments of hub rows are ordered by the neighbours they
+// cover: below it a graph has at most 4 x 2^20 / 32 segments, few enough to be
+// in flight together, and the sort's launches would be a good part of a
+// mini-batch block's build
+constexpr int64_t ORDER_EDGES = (int64_t)1 << 20;
+
+// the longest rows that the edge softmax still gives to one wavefront
+int64_t far_degree(const gnnk_graph* g) { return std::max<int64_t>(g->seg_edges, 2048); }
+
 // bits of a row id below n_rows
 int row_bits(int64_t n_rows) { return key_bits(n_rows > 1 ? (uint64_t)(n_rows - 1) : 0); }
-
-// one traversal direction's derived host state from its sorted degrees
-void schedule_host(Dir& d, int64_t S, std::vector<int32_t>& hub_off) {
-    d.max_deg = d.n_rows ? d.sorted_deg[0] : 0;
-    d.n_nz = d.count_above(0);
-    d.n_hub = d.count_above(S);
-    hub_off.assign((size_t)d.n_hub + 1, 0);
-    for (int64_t k = 0; k < d.n_hub; ++k)
-        hub_off[(size_t)k + 1] = hub_off[(size_t)k] + (int32_t)((d.sorted_deg[(size_t)k] + S - 1) / S);
-    d.n_seg = hub_off[(size_t)d.n_hub];
-}
 
 struct Builder {
     gnnk_graph* g;
@@ -263,7 +256,6 @@ struct Builder {
     uint32_t* scratch = nullptr;
     hipStream_t s;
     hipError_t err = hipSuccess;
-    size_t scratch_words = 0;  // uint32 words of `scratch`
 
     void chk(hipError_t x) {
         if (err == hipSuccess) err = x;
@@ -279,83 +271,38 @@ struct Builder {
         return h;
     }
 
-    // the build's temporaries, a region of the workspace
-    void get_scratch() {
-        scratch = at<uint32_t>(L.tmp);
-        scratch_words = L.tmp_words;
-    }
+    // the build's temporaries, regions of the workspace
+    void get_scratch() { scratch = at<uint32_t>(L.tmp); }
+    uint32_t* edge_tmp(int k) { return at<uint32_t>(L.edge_tmp[k]); }
 
-    // edges sorted stably by `row_of_e`: out = {row, edge id, other endpoint} per position
-    void sort_edges(const int32_t* row_of_e, const int32_t* other_of_e, int bits, const RadixArrays& out,
-                    const RadixArrays& tmp) {
-        const RadixArrays in{const_cast<uint32_t*>(reinterpret_cast<const uint32_t*>(row_of_e)), nullptr,
-                             const_cast<uint32_t*>(reinterpret_cast<const uint32_t*>(other_of_e))};
-        chk(radix_sort(in, out, tmp, g->n_edges, bits, scratch, s));
+    // edges sorted stably by `row_of_e`: {row, edge id, other endpoint} per position
+    static RadixSort edge_sort(const int32_t* row_of_e, const int32_t* other_of_e, int64_t E, int bits,
+                               const RadixArrays& out, const RadixArrays& tmp) {
+        auto u = [](const int32_t* p) { return const_cast<uint32_t*>(reinterpret_cast<const uint32_t*>(p)); };
+        return {{u(row_of_e), nullptr, u(other_of_e)}, out, tmp, E, bits};
     }
-
+    RadixSort in_sort(const int32_t* src_of_e, const int32_t* dst_of_e) {
+        return edge_sort(dst_of_e, src_of_e, g->n_edges, row_bits(g->n_dst),
+                         {at<uint32_t>(L.in_row), at<uint32_t>(L.in_eid), at<uint32_t>(L.in_idx)},
+                         {edge_tmp(2), edge_tmp(3), edge_tmp(4)});
+    }
     // the reverse graph's CSR from the source and destination of every edge id
-    void build_reverse(const int32_t* src_of_e, const int32_t* dst_of_e) {
-        const int64_t E = g->n_edges;
+    RadixSort out_sort(const int32_t* src_of_e, const int32_t* dst_of_e) {
         Dir& d = g->out;
         d.ptr = W + L.out_ptr;
         d.idx = at<int32_t>(L.out_idx);
         d.eid = at<int32_t>(L.out_eid);
         d.row = at<int32_t>(L.out_row);
         d.pos = at<int32_t>(L.out_pos);
-        sort_edges(src_of_e, dst_of_e, row_bits(g->n_src), {at<uint32_t>(L.out_row), at<uint32_t>(L.out_eid),
-                                                            at<uint32_t>(L.out_idx)},
-                   {at<uint32_t>(L.out_pos), at<uint32_t>(L.tmp_a), at<uint32_t>(L.tmp_b)});
-        chk(launch_ptr_from_keys(at<uint32_t>(L.out_row), E, g->n_src, W + L.out_ptr, g->ptr64, s));
-        chk(launch_inverse(at<int32_t>(L.out_eid), E, at<int32_t>(L.out_pos), s));
+        return edge_sort(src_of_e, dst_of_e, g->n_edges, row_bits(g->n_src),
+                         {at<uint32_t>(L.out_row), at<uint32_t>(L.out_eid), at<uint32_t>(L.out_idx)},
+                         {at<uint32_t>(L.out_pos), edge_tmp(0), edge_tmp(1)});
     }
 
-    // degrees and rows by descending degree (ties by row id) on the device;
-    // the sorted degrees are copied into d.sorted_deg (complete after the
-    // next synchronisation of s)
-    void order_rows(Dir& d, std::vector<uint32_t>& keys_h) {
-        const int64_t n = d.n_rows, E = g->n_edges;
-        const int64_t pad = (n + 63) / 64 * 64;
-        uint32_t* key = scratch;
-        uint32_t* sorted = key + pad;
-        uint32_t* tk = sorted + pad;
-        uint32_t* tv = tk + pad;
-        uint32_t* rs = tv + pad;
-        chk(launch_degrees(d.ptr, g->ptr64, n, d.deg, key, (uint32_t)E, s));
-        chk(radix_sort({key, nullptr, nullptr}, {sorted, reinterpret_cast<uint32_t*>(d.perm), nullptr},
-                       {tk, tv, nullptr}, n, key_bits((uint64_t)E), rs, s));
-        keys_h.resize((size_t)n);
-        if (n > 0) chk(hipMemcpyAsync(keys_h.data(), sorted, (size_t)n * 4, hipMemcpyDeviceToHost, s));
-    }
-
-    // The order in which wavefronts take the hub segments of a direction:
-    // by the neighbour ids a segment covers (its key, the halves of its
-    // first and last neighbour id summed), a stable sort, so equal keys keep
-    // table order.  Where rows list their neighbours in ascending order, the
-    // segments that run at the same time then gather from one slice of the
-    // neighbour table; elsewhere the order changes nothing.  Results do not
-    // depend on it (partials are combined in table order).
-    void order_segments(Dir& d, int64_t n_cols) {
-        const int64_t n = d.n_seg;
-        if (n <= 0) return;
-        const int64_t pad = (n + 63) / 64 * 64;
-        // the temporaries are sized for the largest segment count a graph of
-        // this size can have
-        if (4 * (size_t)pad + radix_scratch_words(n) > scratch_words) {
-            if (err == hipSuccess) err = hipErrorInvalidValue;
-            return;
-        }
-        uint32_t* key = scratch;
-        uint32_t* sorted = key + pad;
-        uint32_t* tk = sorted + pad;
-        uint32_t* tv = tk + pad;
-        uint32_t* rs = tv + pad;
-        chk(launch_seg_keys(d.seg, n, d.idx, key, s));
-        chk(radix_sort({key, nullptr, nullptr}, {sorted, reinterpret_cast<uint32_t*>(d.seg_order), nullptr},
-                       {tk, tv, nullptr}, n, row_bits(n_cols), rs, s));
-    }
-
-    // common tail: degree order, identity flag, hub tables
-    gnnk_status finish(size_t ws_bytes, bool check_identity) {
+    // The common tail: row offsets, degrees and rows by descending degree
+    // (ties by row id) of both CSRs, the read-back, and the tables.  coo:
+    // the in-CSR's offsets are not built yet and its edge ids not checked.
+    gnnk_status finish(size_t ws_bytes, bool coo) {
         const int64_t E = g->n_edges;
         Dir& in = g->in;
         Dir& out = g->out;
@@ -365,93 +312,126 @@ struct Builder {
         out.deg = at<int32_t>(L.out_deg);
         in.perm = at<int32_t>(L.in_perm);
         out.perm = at<int32_t>(L.out_perm);
-        std::vector<uint32_t> kin, kout;
-        order_rows(in, kin);
-        order_rows(out, kout);
-        const int32_t h = read_flag();  // also completes the two copies above
+        chk(launch_edge_ids(out.eid, out.pos, coo ? in.eid : nullptr, E, g->flag, FLAG_NOT_IDENT, s));
+        const size_t pi = pad64(g->n_dst), po = pad64(g->n_src);
+        uint32_t* k0 = scratch;            // degree keys: the in-CSR's arrays
+        uint32_t* k1 = scratch + 4 * pi;   // and the reverse CSR's
+        uint32_t* rs = k1 + 4 * po;
+        // (an offset array that the caller gave is only read)
+        chk(launch_rows({coo ? at<uint32_t>(L.in_row) : nullptr, const_cast<void*>(in.ptr), in.deg, k0, in.n_rows},
+                        {at<uint32_t>(L.out_row), const_cast<void*>(out.ptr), out.deg, k1, out.n_rows}, g->ptr64, E,
+                        s));
+        auto by_degree = [&](uint32_t* k, size_t pad, Dir& d) -> RadixSort {
+            return {{k, nullptr, nullptr}, {k + pad, reinterpret_cast<uint32_t*>(d.perm), nullptr},
+                    {k + 2 * pad, k + 3 * pad, nullptr}, d.n_rows, key_bits((uint64_t)E)};
+        };
+        const RadixSort deg_sorts[2] = {by_degree(k0, pi, in), by_degree(k1, po, out)};
+        chk(radix_sort(deg_sorts, 2, rs, s));
+        SummaryArgs sa{};
+        sa.sorted[0] = k0 + pi;
+        sa.sorted[1] = k1 + po;
+        sa.n_rows[0] = in.n_rows;
+        sa.n_rows[1] = out.n_rows;
+        sa.n_edges = E;
+        sa.seg_edges[0] = g->seg_edges;
+        sa.seg_edges[1] = g->seg_edges_in_fine;
+        sa.seg_edges[2] = g->seg_edges_out;
+        sa.seg_edges[3] = g->seg_edges_fine;
+        sa.far[0] = sa.far[1] = in.far_deg = out.far_deg = far_degree(g);
+        sa.out = reinterpret_cast<BuildSummary*>(g->flag);
+        chk(launch_summary(sa, s));
+        BuildSummary sum;
+        chk(hipMemcpyAsync(&sum, g->flag, sizeof(sum), hipMemcpyDeviceToHost, s));
+        chk(hipStreamSynchronize(s));
         if (err != hipSuccess) return hip_fail(err, "graph build");
-        if (check_identity) {
-            g->identity_eids = !(h & FLAG_NOT_IDENT);
+        // nothing so far indexes with an endpoint, so that an edge list is
+        // refused here, in the same read-back
+        if (sum.flag & FLAG_INDEX) return fail(GNNK_EINVAL, "an edge has an endpoint out of range");
+        if (coo) {
+            g->identity_eids = !(sum.flag & FLAG_NOT_IDENT);
             if (g->identity_eids) in.eid = nullptr;
         }
-        in.sorted_deg.resize(kin.size());
-        for (size_t k = 0; k < kin.size(); ++k) in.sorted_deg[k] = (int32_t)((uint32_t)E - kin[k]);
-        out.sorted_deg.resize(kout.size());
-        for (size_t k = 0; k < kout.size(); ++k) out.sorted_deg[k] = (int32_t)((uint32_t)E - kout[k]);
-        std::vector<int32_t>& hin = in.hub_host;
-        std::vector<int32_t>& hout = out.hub_host;
-        schedule_host(in, g->seg_edges, hin);
-        schedule_host(out, g->seg_edges_out, hout);
+        for (int d = 0; d < 2; ++d) {
+            Dir& x = d ? out : in;
+            x.max_deg = sum.max_deg[d];
+            x.n_far = sum.above_far[d];
+            x.above.assign(sum.above[d], sum.above[d] + SUMMARY_DEG + 1);
+            x.n_nz = x.above[0];
+            x.n_hub = sum.n_hub[2 * d];
+            x.n_seg = sum.n_seg[2 * d];
+        }
+        // the finer tables: the same arrays but for the hub rows and segments
         Dir& fine = g->out_fine;
-        const bool finer = g->seg_edges_fine < g->seg_edges_out;
-        fine = out;
-        if (finer) schedule_host(fine, g->seg_edges_fine, fine.hub_host);
         Dir& ifine = g->in_fine;
-        const bool ifiner = g->seg_edges_in_fine < g->seg_edges;
+        const bool finer = g->seg_edges_fine < g->seg_edges_out, ifiner = g->seg_edges_in_fine < g->seg_edges;
+        fine = out;
         ifine = in;
-        if (ifiner) schedule_host(ifine, g->seg_edges_in_fine, ifine.hub_host);
-        L = make_layout(g->n_src, g->n_dst, E, g->ptr64 ? 8 : 4, min_seg_edges(g), in.n_hub, out.n_hub, in.n_seg,
-                        out.n_seg, finer ? fine.n_hub : 0, finer ? fine.n_seg : 0, ifiner ? ifine.n_hub : 0,
+        if (ifiner) {
+            ifine.n_hub = sum.n_hub[1];
+            ifine.n_seg = sum.n_seg[1];
+        }
+        if (finer) {
+            fine.n_hub = sum.n_hub[3];
+            fine.n_seg = sum.n_seg[3];
+        }
+        L = make_layout(g->n_src, g->n_dst, E, g->ptr64 ? 8 : 4, in.n_hub, out.n_hub, in.n_seg, out.n_seg,
+                        finer ? fine.n_hub : 0, finer ? fine.n_seg : 0, ifiner ? ifine.n_hub : 0,
                         ifiner ? ifine.n_seg : 0);
         if (ws_bytes < L.total)
             return fail(GNNK_ENOMEM, "workspace of %zu bytes is smaller than the %zu bytes this graph needs",
                         ws_bytes, L.total);
-        in.hub_off = at<int32_t>(L.in_hub);
-        out.hub_off = at<int32_t>(L.out_hub);
-        in.seg = at<int4>(L.in_seg);
-        out.seg = at<int4>(L.out_seg);
-        in.seg_order = at<int32_t>(L.in_sego);
-        out.seg_order = at<int32_t>(L.out_sego);
-        in.segw = at<int4>(L.in_segw);
-        out.segw = at<int4>(L.out_segw);
-        in.rowt = at<int4>(L.in_rowt);
-        out.rowt = at<int4>(L.out_rowt);
-        chk(launch_row_table(in.ptr, g->ptr64, in.perm, in.n_rows, in.rowt, s));
-        chk(launch_row_table(out.ptr, g->ptr64, out.perm, out.n_rows, out.rowt, s));
-        chk(hipMemcpyAsync(in.hub_off, hin.data(), hin.size() * 4, hipMemcpyHostToDevice, s));
-        chk(hipMemcpyAsync(out.hub_off, hout.data(), hout.size() * 4, hipMemcpyHostToDevice, s));
-        chk(launch_hub_segments(in.ptr, g->ptr64, in.perm, in.hub_off, in.n_hub, g->seg_edges, in.seg, s));
-        chk(launch_hub_segments(out.ptr, g->ptr64, out.perm, out.hub_off, out.n_hub, g->seg_edges_out, out.seg, s));
-        order_segments(in, g->n_src);
-        order_segments(out, g->n_dst);
-        chk(launch_seg_wave(in.seg, in.seg_order, in.n_seg, in.segw, s));
-        chk(launch_seg_wave(out.seg, out.seg_order, out.n_seg, out.segw, s));
-        if (finer) {
-            fine.hub_off = at<int32_t>(L.fine_hub);
-            fine.seg = at<int4>(L.fine_seg);
-            fine.seg_order = at<int32_t>(L.fine_sego);
-            fine.segw = at<int4>(L.fine_segw);
-            fine.rowt = out.rowt;
-            chk(hipMemcpyAsync(fine.hub_off, fine.hub_host.data(), fine.hub_host.size() * 4, hipMemcpyHostToDevice,
-                               s));
-            chk(launch_hub_segments(fine.ptr, g->ptr64, fine.perm, fine.hub_off, fine.n_hub, g->seg_edges_fine,
-                                    fine.seg, s));
-            order_segments(fine, g->n_dst);
-            chk(launch_seg_wave(fine.seg, fine.seg_order, fine.n_seg, fine.segw, s));
-        } else {
-            fine = out;
-        }
-        if (ifiner) {
-            ifine.hub_off = at<int32_t>(L.ifine_hub);
-            ifine.seg = at<int4>(L.ifine_seg);
-            ifine.seg_order = at<int32_t>(L.ifine_sego);
-            ifine.segw = at<int4>(L.ifine_segw);
-            ifine.rowt = in.rowt;
-            chk(hipMemcpyAsync(ifine.hub_off, ifine.hub_host.data(), ifine.hub_host.size() * 4,
-                               hipMemcpyHostToDevice, s));
-            chk(launch_hub_segments(ifine.ptr, g->ptr64, ifine.perm, ifine.hub_off, ifine.n_hub,
-                                    g->seg_edges_in_fine, ifine.seg, s));
-            order_segments(ifine, g->n_src);
-            chk(launch_seg_wave(ifine.seg, ifine.seg_order, ifine.n_seg, ifine.segw, s));
-        } else {
-            ifine = in;
-        }
-        chk(hipMemsetAsync(g->flag, 0, 4, s));
-        // the host copies of the hub offsets stay with the handle, so the
-        // copies above may still be in flight when the call returns
+        in.rowt = ifine.rowt = at<int4>(L.in_rowt);
+        out.rowt = fine.rowt = at<int4>(L.out_rowt);
+        chk(launch_row_table(in.ptr, in.perm, in.n_rows, in.rowt, out.ptr, out.perm, out.n_rows, out.rowt, g->ptr64,
+                             s));
+        HubArgs H{};
+        int64_t n_seg = 0;
+        auto table = [&](int t, Dir& d, bool own, size_t hub, size_t seg, size_t sego, size_t segw, int64_t S) {
+            HubTable& T = H.table[t];
+            T = {d.rowt, d.idx, at<int32_t>(hub), at<int4>(seg), at<int32_t>(sego), at<int4>(segw), own ? d.n_hub : 0,
+                 S, n_seg};
+            if (!own) return;
+            d.hub_off = T.hub_off;
+            d.seg = T.seg;
+            d.seg_order = T.seg_order;
+            d.segw = T.segw;
+            n_seg += d.n_seg;
+        };
+        table(0, in, true, L.in_hub, L.in_seg, L.in_sego, L.in_segw, g->seg_edges);
+        table(1, ifine, ifiner, L.ifine_hub, L.ifine_seg, L.ifine_sego, L.ifine_segw, g->seg_edges_in_fine);
+        table(2, out, true, L.out_hub, L.out_seg, L.out_sego, L.out_segw, g->seg_edges_out);
+        table(3, fine, finer, L.fine_hub, L.fine_seg, L.fine_sego, L.fine_segw, g->seg_edges_fine);
+        if (!ifiner) ifine = in;
+        if (!finer) fine = out;
+        build_segments(H, n_seg);
         if (err != hipSuccess) return hip_fail(err, "graph build");
         g->ws_used = L.total;
         return GNNK_OK;
+    }
+
+    // The segments of hub rows and the order in which wavefronts take them:
+    // by the neighbour ids a segment covers (its key, the halves of its
+    // first and last neighbour id, summed), a stable sort, so equal keys keep
+    // table order.  Where rows list their neighbours in ascending order, the
+    // segments that run at the same time then gather from one slice of the
+    // neighbour table; elsewhere the order changes nothing.  Results do not
+    // depend on it (partials are combined in table order).  Graphs of few
+    // edges keep table order: all their segments are in flight at once.
+    void build_segments(const HubArgs& H, int64_t n_seg) {
+        const bool ordered = n_seg > 0 && g->n_edges >= ORDER_EDGES;
+        // 32-bit keys: ids of more than 30 bits lose their lowest ones
+        const int bits = row_bits(std::max(g->n_src, g->n_dst)), id_bits = std::min(bits, 30);
+        uint32_t* key = ordered ? edge_tmp(0) : nullptr;
+        chk(launch_hub_tables(H, n_seg, id_bits, bits - id_bits, key, s));
+        if (!ordered) {
+            chk(launch_seg_wave(H, n_seg, nullptr, s));
+            return;
+        }
+        // one sort of all tables, the table number above the neighbour ids
+        const RadixSort r{{key, nullptr, nullptr}, {edge_tmp(1), edge_tmp(2), nullptr},
+                          {edge_tmp(3), edge_tmp(4), nullptr}, n_seg, id_bits + 2};
+        chk(radix_sort(&r, 1, scratch, s));
+        chk(launch_seg_wave(H, n_seg, edge_tmp(2), s));
     }
 };
 
@@ -476,7 +456,7 @@ gnnk_graph* new_graph(int64_t num_src, int64_t num_dst, int64_t num_edges, gnnk_
 // workspace checks shared by both constructors; fills b.W, b.L, g->flag
 gnnk_status begin_build(Builder& b, void* ws, size_t ws_bytes) {
     gnnk_graph* g = b.g;
-    b.L = make_layout(g->n_src, g->n_dst, g->n_edges, g->ptr64 ? 8 : 4, min_seg_edges(g), 0, 0, 0, 0);
+    b.L = make_layout(g->n_src, g->n_dst, g->n_edges, g->ptr64 ? 8 : 4, 0, 0, 0, 0);
     if (!ws || ws_bytes < b.L.total)
         return fail(GNNK_ENOMEM, "workspace of %zu bytes is smaller than the %zu bytes this graph needs", ws_bytes,
                     b.L.total);
@@ -492,11 +472,7 @@ gnnk_status create_coo(Builder& b, const int32_t* src, const int32_t* dst, void*
     const int64_t E = g->n_edges;
     gnnk_status st = begin_build(b, ws, ws_bytes);
     if (st != GNNK_OK) return st;
-    b.chk(launch_validate(src, E, g->n_src, g->flag, b.s));
-    b.chk(launch_validate(dst, E, g->n_dst, g->flag, b.s));
-    const int32_t h = b.read_flag();
-    if (b.err != hipSuccess) return hip_fail(b.err, "checking the edge list");
-    if (h & FLAG_INDEX) return fail(GNNK_EINVAL, "an edge has an endpoint out of range");
+    b.chk(launch_validate(src, g->n_src, dst, g->n_dst, E, g->flag, b.s));
     b.get_scratch();
     const Layout& L = b.L;
     Dir& in = g->in;
@@ -504,13 +480,10 @@ gnnk_status create_coo(Builder& b, const int32_t* src, const int32_t* dst, void*
     in.idx = b.at<int32_t>(L.in_idx);
     in.eid = b.at<int32_t>(L.in_eid);
     in.row = b.at<int32_t>(L.in_row);
-    // in-CSR: edges sorted by destination, ties in edge-id order
-    b.sort_edges(dst, src, row_bits(g->n_dst), {b.at<uint32_t>(L.in_row), b.at<uint32_t>(L.in_eid),
-                                                b.at<uint32_t>(L.in_idx)},
-                 {b.at<uint32_t>(L.out_row), b.at<uint32_t>(L.out_eid), b.at<uint32_t>(L.out_idx)});
-    b.chk(launch_ptr_from_keys(b.at<uint32_t>(L.in_row), E, g->n_dst, b.W + L.in_ptr, g->ptr64, b.s));
-    b.chk(launch_check_identity(b.at<int32_t>(L.in_eid), E, g->flag, FLAG_NOT_IDENT, b.s));
-    b.build_reverse(src, dst);
+    // both CSRs in the same launches: edges sorted by destination and by
+    // source, ties in edge-id order
+    const RadixSort sorts[2] = {b.in_sort(src, dst), b.out_sort(src, dst)};
+    b.chk(radix_sort(sorts, 2, b.scratch, b.s));
     return b.finish(ws_bytes, true);
 }
 
@@ -522,10 +495,10 @@ gnnk_status create_csr(Builder& b, const void* indptr, const int32_t* indices, c
     if (st != GNNK_OK) return st;
     const Layout& L = b.L;
     b.chk(launch_validate_ptr(indptr, g->ptr64, g->n_dst, E, g->flag, b.s));
-    b.chk(launch_validate(indices, E, g->n_src, g->flag, b.s));
+    b.chk(launch_validate(indices, g->n_src, nullptr, 0, E, g->flag, b.s));
     if (eids) {
         b.chk(launch_check_permutation(eids, E, b.at<uint32_t>(L.out_pos), g->flag, FLAG_PERM, b.s));
-        b.chk(launch_check_identity(eids, E, g->flag, FLAG_NOT_IDENT, b.s));
+        b.chk(launch_edge_ids(nullptr, nullptr, eids, E, g->flag, FLAG_NOT_IDENT, b.s));
     }
     const int32_t h = b.read_flag();
     if (b.err != hipSuccess) return hip_fail(b.err, "checking the CSR");
@@ -542,14 +515,15 @@ gnnk_status create_csr(Builder& b, const void* indptr, const int32_t* indices, c
     in.eid = identity ? nullptr : eids;
     in.row = b.at<int32_t>(L.in_row);
     b.chk(launch_fill_rows(indptr, g->ptr64, g->n_dst, E, in.row, b.s));
-    if (identity) {
-        b.build_reverse(indices, in.row);
-    } else {
-        int32_t* src_of_e = b.at<int32_t>(L.in_idx);
-        int32_t* dst_of_e = b.at<int32_t>(L.in_eid);
-        b.chk(launch_edge_ends(indices, eids, in.row, E, src_of_e, dst_of_e, b.s));
-        b.build_reverse(src_of_e, dst_of_e);
+    const int32_t* src_of_e = indices;
+    const int32_t* dst_of_e = in.row;
+    if (!identity) {
+        b.chk(launch_edge_ends(indices, eids, in.row, E, b.at<int32_t>(L.in_idx), b.at<int32_t>(L.in_eid), b.s));
+        src_of_e = b.at<int32_t>(L.in_idx);
+        dst_of_e = b.at<int32_t>(L.in_eid);
     }
+    const RadixSort sort = b.out_sort(src_of_e, dst_of_e);
+    b.chk(radix_sort(&sort, 1, b.scratch, b.s));
     return b.finish(ws_bytes, false);
 }
 
@@ -570,8 +544,8 @@ gnnk_status graph_workspace_bytes(int64_t num_src, int64_t num_dst, int64_t num_
     // E / S + (hub rows) <= 2 E / S segments
     const int64_t Si = seg_edges_for(num_edges, false), So = seg_edges_for(num_edges, true);
     const int64_t Sf = seg_edges_fine_for(num_edges);  // both CSRs' finer tables
-    Layout L = make_layout(num_src, num_dst, num_edges, ptr_t == GNNK_I64 ? 8 : 4, std::min({Si, So, Sf}),
-                           num_edges / Si + 1, num_edges / So + 1, max_segments(num_edges, Si),
+    Layout L = make_layout(num_src, num_dst, num_edges, ptr_t == GNNK_I64 ? 8 : 4, num_edges / Si + 1,
+                           num_edges / So + 1, max_segments(num_edges, Si),
                            max_segments(num_edges, So), Sf < So ? num_edges / Sf + 1 : 0,
                            Sf < So ? max_segments(num_edges, Sf) : 0, Sf < Si ? num_edges / Sf + 1 : 0,
                            Sf < Si ? max_segments(num_edges, Sf) : 0);
@@ -683,10 +657,8 @@ gnnk_status graph_validate(gnnk_graph_t g, hipStream_t stream) {
     const int64_t E = g->n_edges;
     if (e == hipSuccess) e = launch_validate_ptr(g->in.ptr, g->ptr64, g->n_dst, E, g->flag, stream);
     if (e == hipSuccess) e = launch_validate_ptr(g->out.ptr, g->ptr64, g->n_src, E, g->flag, stream);
-    if (e == hipSuccess) e = launch_validate(g->in.idx, E, g->n_src, g->flag, stream);
-    if (e == hipSuccess) e = launch_validate(g->out.idx, E, g->n_dst, g->flag, stream);
-    if (e == hipSuccess && g->in.eid) e = launch_validate(g->in.eid, E, E, g->flag, stream);
-    if (e == hipSuccess) e = launch_validate(g->out.eid, E, E, g->flag, stream);
+    if (e == hipSuccess) e = launch_validate(g->in.idx, g->n_src, g->out.idx, g->n_dst, E, g->flag, stream);
+    if (e == hipSuccess) e = launch_validate(g->out.eid, E, g->in.eid, E, E, g->flag, stream);
     int32_t h = 0;
     if (e == hipSuccess) e = hipMemcpyAsync(&h, g->flag, 4, hipMemcpyDeviceToHost, stream);
     if (e == hipSuccess) e = hipStreamSynchronize(stream);

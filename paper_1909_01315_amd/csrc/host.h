@@ -31,8 +31,8 @@ struct Dir {
     int32_t* row = nullptr;        // device row of each position (COO form)
     int32_t* pos = nullptr;        // device position of each edge id in this CSR
     int64_t n_seg = 0, n_hub = 0, n_nz = 0, max_deg = 0;
-    std::vector<int32_t> sorted_deg;  // host, descending (bin boundaries by binary search)
-    std::vector<int32_t> hub_host;    // host copy of hub_off (the source of its upload)
+    int64_t far_deg = 0, n_far = 0;   // a threshold past the ones of `above`, and the rows longer than it
+    std::vector<int32_t> above;       // host: rows of more than t edges, t = 0..SUMMARY_DEG
     int64_t count_above(int64_t t) const;  // rows with degree > t
 };
 

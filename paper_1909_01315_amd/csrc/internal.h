@@ -232,12 +232,12 @@ hipError_t launch_sddmm(const EngineArgs& a, int dtype, int vec, int opk, int sp
 hipError_t launch_softmax(const EngineArgs& a, int dtype, int vec, bool backward, hipStream_t s);
 hipError_t launch_leaky(const void* x, const void* dy, void* y, int64_t rows, int32_t cols, int64_t sx,
                         int64_t sdy, int64_t sy, float slope, int dtype, bool backward, hipStream_t s);
-hipError_t launch_validate(const int32_t* idx, int64_t n, int64_t bound, int32_t* flag, hipStream_t s);
+// every a[i] in [0, bound_a) and, unless b is nullptr, b[i] in [0, bound_b)
+hipError_t launch_validate(const int32_t* a, int64_t bound_a, const int32_t* b, int64_t bound_b, int64_t n,
+                           int32_t* flag, hipStream_t s);
 hipError_t launch_validate_ptr(const void* ptr, int ptr64, int64_t n_rows, int64_t n_edges, int32_t* flag,
                                hipStream_t s);
 hipError_t launch_iota(int32_t* out, int64_t n, hipStream_t s);
-// pos[perm[q]] = q for q < n
-hipError_t launch_inverse(const int32_t* perm, int64_t n, int32_t* pos, hipStream_t s);
 // Winner masks of max/min: bits[pos_of_edge[e] * words + c / 32] has bit c % 32
 // set iff arg_e[v * ld + c] == e for some row v and column c < D (zeroed first).
 hipError_t launch_winner_bits(const int32_t* arg_e, int64_t n_rows, int32_t D, int64_t ld,
@@ -262,44 +262,87 @@ hipError_t launch_winner_rows(const WinnerRowsArgs& a, int ptr64, int64_t n_edge
 hipError_t launch_copy_ptr(const void* src, int src64, void* dst, int dst64, int64_t n, hipStream_t s);
 
 // ----- device construction of the graph formats (build.hip) -----
-// key[k] = idx[seg[k].begin] / 2 + idx[seg[k].end - 1] / 2 for k < n_seg
-hipError_t launch_seg_keys(const int4* seg, int64_t n_seg, const int32_t* idx, uint32_t* key, hipStream_t s);
-hipError_t launch_seg_wave(const int4* seg, const int32_t* order, int64_t n_seg, int4* segw, hipStream_t s);
-hipError_t launch_row_table(const void* ptr, int ptr64, const int32_t* perm, int64_t n_rows, int4* rowt,
-                            hipStream_t s);
 // bits needed for keys in [0, max_key]
 int key_bits(uint64_t max_key);
-// uint32 words of scratch radix_sort needs for n keys
-size_t radix_scratch_words(int64_t n);
 // keys and the one or two arrays of values that move with them
 struct RadixArrays {
     uint32_t* key;
     uint32_t* v0;
     uint32_t* v1;  // nullptr: one array of values
 };
-// Stable sort of n keys and their values by the low `bits` bits of the key.
+// A stable sort of n keys and their values by the low `bits` bits of the key.
 // in is only read (in.v0 == nullptr stands for 0..n-1); the result lands in
-// out, whose key may be nullptr where bits needs at most two passes; tmp (n
-// entries each, used from two passes on) and scratch are clobbered.  No
+// out, whose key may be nullptr where the sort takes at most two passes of 9
+// bits; tmp (n entries each, used from two passes on) is clobbered.  No
 // array may alias another.
-hipError_t radix_sort(const RadixArrays& in, const RadixArrays& out, const RadixArrays& tmp, int64_t n, int bits,
-                      uint32_t* scratch, hipStream_t s);
-// ptr[r] = first position of the sorted keys that is >= r, r in [0, n_rows]
-hipError_t launch_ptr_from_keys(const uint32_t* keys, int64_t n_keys, int64_t n_rows, void* ptr, int ptr64,
-                                hipStream_t s);
-// deg[r] = ptr[r + 1] - ptr[r]; deg_key[r] = cap - deg[r]
-hipError_t launch_degrees(const void* ptr, int ptr64, int64_t n_rows, int32_t* deg, uint32_t* deg_key, uint32_t cap,
-                          hipStream_t s);
-// flag |= bit unless eid[p] == p for every p
-hipError_t launch_check_identity(const int32_t* eid, int64_t n, int32_t* flag, int32_t bit, hipStream_t s);
+struct RadixSort {
+    RadixArrays in, out, tmp;
+    int64_t n;
+    int bits;
+};
+// uint32 words of scratch radix_sort needs for sorts of n0 and n1 keys
+size_t radix_scratch_words(int64_t n0, int64_t n1);
+// one or two such sorts (of the same number of arrays) in the same launches
+hipError_t radix_sort(const RadixSort* sorts, int n_sorts, uint32_t* scratch, hipStream_t s);
+// row offsets, degrees and degree keys (n_edges - degree) of both CSRs
+struct RowsJob {
+    const uint32_t* key;  // row of every position, ascending; nullptr: ptr is given
+    void* ptr;
+    int32_t* deg;
+    uint32_t* deg_key;
+    int64_t n_rows;
+};
+hipError_t launch_rows(const RowsJob& a, const RowsJob& b, int ptr64, int64_t n_edges, hipStream_t s);
+// pos[out_eid[p]] = p; flag |= bit unless in_eid[p] == p for every p (either
+// id array may be nullptr)
+hipError_t launch_edge_ids(const int32_t* out_eid, int32_t* pos, const int32_t* in_eid, int64_t n, int32_t* flag,
+                           int32_t bit, hipStream_t s);
+// What the host reads back of a build: the flag word, and of each direction's
+// degrees what places the role boundaries of the schedules.  Directions: 0
+// the in-CSR, 1 the reverse CSR; tables: 0 the in-CSR's segments, 1 its finer
+// ones, 2 and 3 the same of the reverse CSR.
+constexpr int SUMMARY_DEG = 4096;  // the largest threshold the small-row option takes
+constexpr int SUMMARY_TABLES = 4;
+struct BuildSummary {
+    int32_t flag;
+    int32_t n_hub[SUMMARY_TABLES], n_seg[SUMMARY_TABLES];
+    int32_t max_deg[2];
+    int32_t above_far[2];                 // rows of more than SummaryArgs::far edges
+    int32_t above[2][SUMMARY_DEG + 1];    // rows of more than t edges
+};
+struct SummaryArgs {
+    const uint32_t* sorted[2];  // ascending degree keys
+    int64_t n_rows[2];
+    int64_t n_edges;
+    int64_t seg_edges[SUMMARY_TABLES];
+    int64_t far[2];
+    BuildSummary* out;
+};
+hipError_t launch_summary(const SummaryArgs& a, hipStream_t s);
+// the hub tables of a graph: offsets and segments (with the sort keys of the
+// segment order, key == nullptr: none), then the order of the wavefronts
+struct HubTable {
+    const int4* rowt;
+    const int32_t* idx;
+    int32_t* hub_off;
+    int4* seg;
+    int32_t* seg_order;
+    int4* segw;
+    int64_t n_hub, seg_edges;
+    int64_t base;  // first entry in the concatenation of the tables
+};
+struct HubArgs {
+    HubTable table[SUMMARY_TABLES];
+};
+hipError_t launch_hub_tables(const HubArgs& a, int64_t n_seg, int id_bits, int drop, uint32_t* key, hipStream_t s);
+hipError_t launch_seg_wave(const HubArgs& a, int64_t n_seg, const uint32_t* order, hipStream_t s);
+hipError_t launch_row_table(const void* ptr0, const int32_t* perm0, int64_t n0, int4* rowt0, const void* ptr1,
+                            const int32_t* perm1, int64_t n1, int4* rowt1, int ptr64, hipStream_t s);
 // flag |= bit unless eid is a permutation of 0..n-1 (counts: n words of scratch)
 hipError_t launch_check_permutation(const int32_t* eid, int64_t n, uint32_t* counts, int32_t* flag, int32_t bit,
                                     hipStream_t s);
 // src_of_e[eid[p]] = idx[p], dst_of_e[eid[p]] = row[p]
 hipError_t launch_edge_ends(const int32_t* idx, const int32_t* eid, const int32_t* row, int64_t n, int32_t* src_of_e,
                             int32_t* dst_of_e, hipStream_t s);
-// segments of the hub rows perm[0, n_hub), starting at seg[hub_off[k]]
-hipError_t launch_hub_segments(const void* ptr, int ptr64, const int32_t* perm, const int32_t* hub_off, int64_t n_hub,
-                               int64_t seg_edges, int4* seg, hipStream_t s);
 
 }  // namespace gnnk

@@ -78,10 +78,16 @@ __global__ __launch_bounds__(256) void leaky_flat_kernel(const T* x, const T* dy
     }
 }
 
-__global__ void validate_kernel(const int32_t* idx, int64_t n, int64_t bound, int32_t* flag) {
+__global__ void validate_kernel(const int32_t* a, int64_t bound_a, const int32_t* b, int64_t bound_b, int64_t n,
+                                int32_t* flag) {
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-        int32_t v = idx[i];
-        if (v < 0 || v >= bound) atomicOr(flag, 1);
+        const int32_t v = a[i];
+        bool bad = v < 0 || v >= bound_a;
+        if (b) {
+            const int32_t w = b[i];
+            bad |= w < 0 || w >= bound_b;
+        }
+        if (bad) atomicOr(flag, 1);
     }
 }
 
@@ -109,11 +115,6 @@ __global__ void fill_rows_kernel(const P* ptr, int64_t n_rows, int64_t n_edges, 
         }
         row[p] = (int32_t)lo;
     }
-}
-
-__global__ void inverse_kernel(const int32_t* perm, int64_t n, int32_t* pos) {
-    for (int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; q < n; q += (int64_t)gridDim.x * blockDim.x)
-        pos[perm[q]] = (int32_t)q;
 }
 
 __global__ void zero_words_kernel(uint32_t* w, int64_t n) {
@@ -276,9 +277,10 @@ hipError_t launch_leaky(const void* x, const void* dy, void* y, int64_t rows, in
     return hipGetLastError();
 }
 
-hipError_t launch_validate(const int32_t* idx, int64_t n, int64_t bound, int32_t* flag, hipStream_t s) {
+hipError_t launch_validate(const int32_t* a, int64_t bound_a, const int32_t* b, int64_t bound_b, int64_t n,
+                           int32_t* flag, hipStream_t s) {
     if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(validate_kernel, dim3(grid_1d(n)), dim3(256), 0, s, idx, n, bound, flag);
+    hipLaunchKernelGGL(validate_kernel, dim3(grid_1d(n)), dim3(256), 0, s, a, bound_a, b, bound_b, n, flag);
     return hipGetLastError();
 }
 
@@ -303,12 +305,6 @@ hipError_t launch_fill_rows(const void* ptr, int ptr64, int64_t n_rows, int64_t 
     else
         hipLaunchKernelGGL(fill_rows_kernel<int32_t>, dim3(grid_1d(n_edges)), dim3(256), 0, s,
                            reinterpret_cast<const int32_t*>(ptr), n_rows, n_edges, row);
-    return hipGetLastError();
-}
-
-hipError_t launch_inverse(const int32_t* perm, int64_t n, int32_t* pos, hipStream_t s) {
-    if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(inverse_kernel, dim3(grid_1d(n)), dim3(256), 0, s, perm, n, pos);
     return hipGetLastError();
 }
 

@@ -1,8 +1,8 @@
 """Device construction of the graph formats against the oracle's CSR (a stable
 counting sort by row written from the definition): offsets, indices, edge
 ids, degrees and the schedule counts compare bit for bit.  The shapes cover
-every number of radix passes of the row sorts (one row: none; up to 2^8,
-2^16, 2^24 and more rows: one to four), ragged last tiles, a single hot row,
+every number of radix passes of the row sorts (one row: one copying pass; up to 2^9,
+2^18, 2^27 rows: one to three), ragged last tiles, a single hot row,
 unsorted edge lists (non-identity edge ids), int64 offsets, and the error
 paths of both constructors."""
 import numpy as np
@@ -33,11 +33,11 @@ def random_edges(seed, n_src, n_dst, E, sort_by_dst=False):
 
 
 @pytest.mark.parametrize("n_src,n_dst,E", [
-    (1, 1, 5000),            # one row each way: no radix pass
+    (1, 1, 5000),            # one row each way: one copying pass
     (7, 250, 10000),         # one pass
-    (300, 70000, 12289),     # two and three passes, ragged last tile
-    (2 ** 24 + 5, 1000, 20000),   # four passes for the reverse graph
-    (1000, 2 ** 24 + 3, 9000),    # four passes for the in-CSR, mostly empty rows
+    (300, 70000, 12289),     # one and two passes, ragged last tile
+    (2 ** 24 + 5, 1000, 20000),   # three passes for the reverse graph
+    (1000, 2 ** 24 + 3, 9000),    # three passes for the in-CSR, mostly empty rows
     (50, 60, 1),
     (4096, 4096, 4096 * 3),  # whole tiles
 ])
@@ -45,6 +45,31 @@ def test_formats_every_pass_count(n_src, n_dst, E):
     src, dst = random_edges(n_src + n_dst + E, n_src, n_dst, E)
     p = Pair(src, dst, n_src, n_dst)
     check_formats(p)
+
+
+@pytest.mark.parametrize("E", [
+    2048, 2049,                     # one tile of the smaller sort, one key more
+    64 * 2048, 64 * 2048 + 1,       # the most keys of the smaller tiles; the larger tiles
+    64 * 8192, 64 * 8192 + 1,       # counts added up by every workgroup; counts scanned
+    (1 << 20) - 1, (1 << 20),       # segments in table order; ordered by the neighbours they cover
+])
+def test_formats_at_the_sort_limits(E):
+    """Both CSRs at the edge counts where the sorts change tiles, the scan
+    and the segment order, with hub rows on both sides and few bits on one
+    (the two directions' sorts share their passes)."""
+    n_src, n_dst = 70001, 300
+    rng = np.random.default_rng(E)
+    src = rng.integers(0, n_src, E).astype(np.int32)
+    dst = rng.integers(0, n_dst, E).astype(np.int32)
+    src[rng.random(E) < 0.3] = 17
+    p = Pair(src, dst, n_src, n_dst)
+    check_formats(p)
+    X = rng.standard_normal((n_src, 1, 4)).astype(np.float32)
+    assert_close(gnnk.gspmm(p.g, "copy_lhs", "sum", dev(X)), orc.gspmm(p.o, "copy_lhs", "sum", X))
+    dZ = rng.standard_normal((n_dst, 1, 4)).astype(np.float32)
+    dX, _ = gnnk.gspmm_backward(p.g, "copy_lhs", "sum", dev(X), None, dev(dZ))
+    ref, _ = orc.gspmm_backward(p.o, "copy_lhs", "sum", X, None, dZ)
+    assert_close(dX, ref)
 
 
 @pytest.mark.parametrize("ptr64", [False, True])
