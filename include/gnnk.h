@@ -134,7 +134,11 @@ typedef struct {
  * ascending order (an edge list sorted by destination, then source) the
  * segments processed at the same time gather from one slice of the neighbour
  * table.  The order never changes a result: segment partials are combined in
- * table order (graphs of fewer than 2^20 edges keep table order).
+ * table order (graphs of fewer than 2^20 edges keep table order).  A graph
+ * of at least 2^20 edges whose edge ids are scattered over its rows, a
+ * quarter of its edges in long rows, also keeps each row listed by neighbour
+ * id (16 bytes per edge of the workspace), and the passes that gather node
+ * rows reduce in that order, which is as fixed as the edge-id order.
  * The call synchronises `stream` once, to read back the input check and what
  * the schedules need of the sorted degrees, and graph_create_csr once more
  * before it, to refuse row offsets that cannot be walked; it allocates no

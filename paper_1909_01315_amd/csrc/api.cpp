@@ -135,11 +135,13 @@ gnnk_status out_desc(const gnnk_tensor* t, Kind k, const Geo& g, OutDev& o) {
     return GNNK_OK;
 }
 
-CsrDev csr_of(const gnnk_graph* g, const Dir& d) {
+// ids: the pass reads or writes edges by id; without, a walk forms no ids
+// beside its positions (and loads none where the graph's are explicit)
+CsrDev csr_of(const gnnk_graph* g, const Dir& d, bool ids = true) {
     CsrDev c{};
     c.ptr = d.ptr;
     c.idx = d.idx;
-    c.eid = d.eid;
+    c.eid = ids ? d.eid : nullptr;
     c.perm = d.perm;
     c.seg = d.seg;
     c.seg_order = d.seg_order;
@@ -217,7 +219,7 @@ bool fits32(const OperandDev& o, int64_t rows, int es) {
 
 // rows of the table an operand reads during a walk over `d`
 int64_t table_rows(const gnnk_graph* g, const Dir& d, int32_t target) {
-    const bool in = &d == &g->in || &d == &g->in_fine;
+    const bool in = !d.reverse;
     if (target == T_EDGE) return g->n_edges;
     if (target == T_NBR) return in ? g->n_src : g->n_dst;
     return in ? g->n_dst : g->n_src;
@@ -316,7 +318,8 @@ void set_edge_chunks(EngineArgs& A, int64_t E, const Geo& geo) {
 // *fused_dw tells whether it was written (else the caller runs its g-SDDMM)
 gnnk_status run_spmm_sum(gnnk_graph* g, const Dir& d, EngineArgs& A, const Geo& geo, int dtype, int opk,
                          hipStream_t s, Scratch& sc, bool* fused_dw = nullptr) {
-    A.csr = csr_of(g, d);
+    auto edges = [](const OperandDev& o) { return o.data && o.target == T_EDGE; };
+    A.csr = csr_of(g, d, edges(A.a) || edges(A.b) || edges(A.c) || (A.flags & F_MASK_A) || fused_dw);
     set_geo(A, geo);
     A.sch = schedule(d, geo, true);
     A.partial_stride = geo.D;
@@ -368,7 +371,8 @@ gnnk_status run_spmm_sum(gnnk_graph* g, const Dir& d, EngineArgs& A, const Geo& 
 gnnk_status run_sddmm(gnnk_graph* g, EngineArgs& A, const Geo& geo, int dtype, int opk, hipStream_t s, Scratch& sc) {
     // the in-CSR's finer segments (c3 u_dot_v 3.33 -> 3.19 ms): a g-SDDMM
     // leaves no partials, and more of each hub row runs in narrow pieces
-    const Dir& d = g->in_fine;
+    const bool gathers = (A.a.data && A.a.target == T_NBR) || (A.b.data && A.b.target == T_NBR);
+    const Dir& d = gathers ? g->in_fine_nbr : g->in_fine;
     A.csr = csr_of(g, d);
     set_geo(A, geo);
     A.sch = schedule(d, geo, false);
@@ -494,7 +498,7 @@ gnnk_status gspmm_impl(gnnk_graph_t g, gnnk_binop op, gnnk_reduce reduce, const 
     // copy_u/mean 2.59 -> 2.46 ms, c4 copy_u/sum 3.59 -> 3.24 ms); copy_e
     // reductions keep the coarser ones, on which they run faster
     const bool gathers = (A.a.target == T_NBR && A.a.full) || (A.b.data && A.b.target == T_NBR && A.b.full);
-    const Dir& d = gathers ? g->in_fine : g->in;
+    const Dir& d = gathers ? g->in_fine_nbr : g->in;
     if (!cmp) return run_spmm_sum(g, d, A, geo, dtype_code(out), opk, stream, sc);
     A.arg_nbr = arg_lhs;
     A.arg_edge = arg_rhs;
@@ -746,11 +750,11 @@ static gnnk_status spmm_backward(gnnk_graph_t g, gnnk_binop op, gnnk_reduce redu
                 W.n_seg = g->in.n_seg;
                 W.n_hub = g->in.n_hub;
                 W.n_small = g->in.n_nz - g->in.n_hub;
-                W.pos = g->out.pos;
+                W.pos = g->out_nbr.pos;
                 W.bits = bits;
                 le = launch_winner_rows(W, g->ptr64, g->n_edges, stream);
             } else {
-                le = launch_winner_bits(arg_rhs, g->n_dst, (int32_t)geo.D, ld, g->out.pos, bits, g->n_edges, words,
+                le = launch_winner_bits(arg_rhs, g->n_dst, (int32_t)geo.D, ld, g->out_nbr.pos, bits, g->n_edges, words,
                                         stream);
             }
             st = launch_status(le, "winner mask launch");
@@ -782,7 +786,7 @@ static gnnk_status spmm_backward(gnnk_graph_t g, gnnk_binop op, gnnk_reduce redu
         }
         // node rows gathered in the finer segments; the argmax scatter, which
         // reads its masks in order and gathers few rows, keeps the coarse ones
-        st = run_spmm_sum(g, cmp ? g->out : g->out_fine, A, geo, dt, opk, stream, sc, want_dw ? &dw_done : nullptr);
+        st = run_spmm_sum(g, cmp ? g->out_nbr : g->out_fine_nbr, A, geo, dt, opk, stream, sc, want_dw ? &dw_done : nullptr);
         if (st != GNNK_OK) return st;
     }
     if (grad_rhs && g->n_edges > 0 && !dw_done) {
@@ -940,7 +944,7 @@ static gnnk_status sddmm_backward(gnnk_graph_t g, gnnk_binop op, const gnnk_tens
         // takes its CSR's finer segments; copy_e sums the coarse ones
         const bool gathers = (A.a.target == T_NBR && A.a.full) || (A.b.data && A.b.target == T_NBR && A.b.full);
         if (tx == GNNK_EDGE) st = run_sddmm(g, A, geo, dt, opk, stream, sc);
-        else st = run_spmm_sum(g, tx == GNNK_SRC ? (gathers ? g->out_fine : g->out) : (gathers ? g->in_fine : g->in),
+        else st = run_spmm_sum(g, tx == GNNK_SRC ? (gathers ? g->out_fine_nbr : g->out) : (gathers ? g->in_fine_nbr : g->in),
                                A, geo, dt, opk, stream, sc);
         if (st != GNNK_OK) return st;
     }
@@ -1033,9 +1037,9 @@ gnnk_status gat_aggregate(gnnk_graph_t g, const gnnk_tensor* feat, const gnnk_te
     A.out.data = out->data;
     A.out.stride = out->row_stride;
     A.out.red = 1;
-    A.csr = csr_of(g, g->in);
+    A.csr = csr_of(g, g->in_nbr, attn != nullptr);
     set_geo(A, geo);
-    A.sch = schedule(g->in, geo, true);
+    A.sch = schedule(g->in_nbr, geo, true);
     const int dt = dtype_code(out);
     const size_t part = (size_t)A.sch.n_seg * 3 * geo.D * 8, ml = attn ? (size_t)A.sch.n_hub * 2 * geo.D * 8 : 0;
     void* row_ml = nullptr;
@@ -1076,12 +1080,12 @@ static gnnk_status gat_bwd_run(gnnk_graph_t g, const gnnk_tensor* feat, const gn
     ain.a = operand(feat, K_FULL, T_NBR);
     ain.b = operand(el, ms[1].kind, T_NBR);
     ain.op = M_MUL;
-    ain.csr = csr_of(g, g->in);
+    ain.csr = csr_of(g, g->in_nbr, false);
     set_geo(ain, geo);
-    ain.sch = schedule(g->in, geo, true);
-    aout.csr = csr_of(g, g->out_fine);
+    ain.sch = schedule(g->in_nbr, geo, true);
+    aout.csr = csr_of(g, g->out_fine_nbr, false);
     set_geo(aout, geo);
-    aout.sch = schedule(g->out_fine, geo, true);
+    aout.sch = schedule(g->out_fine_nbr, geo, true);
     const size_t pa = (size_t)ain.sch.n_seg * 3 * H * 8, pb = (size_t)aout.sch.n_seg * (geo.D + H) * 8;
     double* part = reinterpret_cast<double*>(sc.take(std::max(pa, pb) + 8));
     if (!part) return scratch_fail(sc);

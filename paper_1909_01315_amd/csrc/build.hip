@@ -393,7 +393,8 @@ __global__ void edge_ends_kernel(const int32_t* idx, const int32_t* eid, const i
 
 // What the host needs to know of the sorted degrees (BuildSummary in
 // internal.h).  Workgroups 0..3: hub rows and segments of the four tables;
-// the others: rows of more than t edges, t = 0..SUMMARY_DEG, both directions.
+// the next ones: how close a row's edge ids lie; the others: rows of more than
+// t edges, t = 0..SUMMARY_DEG, both directions.
 __device__ __forceinline__ int64_t rows_above(const uint32_t* sorted, int64_t n_rows, int64_t E, int64_t t) {
     if (t >= E) return 0;
     const uint32_t key = (uint32_t)(E - t);  // keys are E - degree, ascending
@@ -407,6 +408,7 @@ __device__ __forceinline__ int64_t rows_above(const uint32_t* sorted, int64_t n_
 }
 
 constexpr int SUMMARY_BLOCK = 256;
+static_assert(SUMMARY_SAMPLES % SUMMARY_BLOCK == 0, "whole workgroups sample");
 
 __global__ __launch_bounds__(SUMMARY_BLOCK) void summary_kernel(SummaryArgs A) {
     if (blockIdx.x < SUMMARY_TABLES) {
@@ -430,7 +432,21 @@ __global__ __launch_bounds__(SUMMARY_BLOCK) void summary_kernel(SummaryArgs A) {
         }
         return;
     }
-    const int i = (int)(blockIdx.x - SUMMARY_TABLES) * SUMMARY_BLOCK + (int)threadIdx.x;
+    int i = (int)(blockIdx.x - SUMMARY_TABLES) * SUMMARY_BLOCK + (int)threadIdx.x;
+    if (i < SUMMARY_SAMPLES) {
+        // evenly spaced in-CSR positions whose next edge id lies on the same
+        // or the next lines of an edge tensor
+        bool near = false;
+        if (A.eid && A.n_edges > 1) {
+            const int64_t p = (int64_t)i * (A.n_edges - 1) / SUMMARY_SAMPLES;
+            const int64_t d = (int64_t)A.eid[p + 1] - (int64_t)A.eid[p];
+            near = d >= -32 && d <= 32;
+        }
+        const uint64_t m = __ballot(near);
+        if (m != 0ull && (threadIdx.x & 63) == 0) atomicAdd(&A.out->near_ids, __popcll(m));
+        return;
+    }
+    i -= SUMMARY_SAMPLES;
     const int d = i >= SUMMARY_DEG + 1;
     const int t = d ? i - (SUMMARY_DEG + 1) : i;
     if (t > SUMMARY_DEG) return;
@@ -544,12 +560,14 @@ size_t radix_scratch_words(int64_t n0, int64_t n1) {
     return (size_t)(hist + tiles_of(hist, SCAN_TILE) + 64);
 }
 
+int radix_passes(int bits) { return std::max(1, (bits + RS_BITS - 1) / RS_BITS); }
+
 hipError_t radix_sort(const RadixSort* sorts, int n_sorts, uint32_t* scratch, hipStream_t s) {
     int64_t most = 0;
     int passes = 1;
     for (int q = 0; q < n_sorts; ++q) {
         most = std::max(most, sorts[q].n);
-        if (sorts[q].n > 0) passes = std::max(passes, (sorts[q].bits + RS_BITS - 1) / RS_BITS);
+        if (sorts[q].n > 0) passes = std::max(passes, radix_passes(sorts[q].bits));
     }
     if (most <= 0) return hipSuccess;
     const int steps = rs_steps(most);
@@ -624,7 +642,7 @@ hipError_t launch_edge_ids(const int32_t* out_eid, int32_t* pos, const int32_t* 
 }
 
 hipError_t launch_summary(const SummaryArgs& a, hipStream_t s) {
-    const unsigned n = SUMMARY_TABLES + tiles_of(2 * (SUMMARY_DEG + 1), SUMMARY_BLOCK);
+    const unsigned n = SUMMARY_TABLES + tiles_of(SUMMARY_SAMPLES + 2 * (SUMMARY_DEG + 1), SUMMARY_BLOCK);
     hipLaunchKernelGGL(summary_kernel, dim3(n), dim3(SUMMARY_BLOCK), 0, s, a);
     return hipGetLastError();
 }

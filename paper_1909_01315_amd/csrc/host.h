@@ -17,6 +17,7 @@ namespace gnnk {
 // One traversal direction: the in-CSR (rows = destinations) or the reverse
 // graph's CSR (rows = sources).
 struct Dir {
+    bool reverse = false;          // the reverse graph's CSR
     int64_t n_rows = 0;
     const void* ptr = nullptr;     // device row offsets (graph ptr type)
     const int32_t* idx = nullptr;  // device neighbour ids
@@ -29,7 +30,7 @@ struct Dir {
     int4* rowt = nullptr;          // device {perm[k], begin, end, 0} per degree-order position
     int32_t* hub_off = nullptr;    // device first segment per hub row (n_hub + 1)
     int32_t* row = nullptr;        // device row of each position (COO form)
-    int32_t* pos = nullptr;        // device position of each edge id in this CSR
+    int32_t* pos = nullptr;        // device position of each edge id in out_nbr (reverse CSRs)
     int64_t n_seg = 0, n_hub = 0, n_nz = 0, max_deg = 0;
     int64_t far_deg = 0, n_far = 0;   // a threshold past the ones of `above`, and the rows longer than it
     std::vector<int32_t> above;       // host: rows of more than t edges, t = 0..SUMMARY_DEG
@@ -53,6 +54,10 @@ struct gnnk_graph {
     // the reverse graph's CSR with segments of seg_edges_fine edges (its own
     // hub tables and segment order, every other array shared with `out`)
     gnnk::Dir out_fine;
+    // The same four with each row listed by neighbour id, for the passes that
+    // gather node rows; the four above where the graph has no such listing.
+    // A pass over these reaches edges through eid in any order.
+    gnnk::Dir in_nbr, in_fine_nbr, out_nbr, out_fine_nbr;
     int32_t* flag = nullptr;  // device word for graph_validate
     size_t ws_used = 0;
     // scratch buffers the caller lent to the handle, one per stream

@@ -274,12 +274,15 @@ struct RadixArrays {
 // in is only read (in.v0 == nullptr stands for 0..n-1); the result lands in
 // out, whose key may be nullptr where the sort takes at most two passes of 9
 // bits; tmp (n entries each, used from two passes on) is clobbered.  No
-// array may alias another.
+// array may alias another (an input array may serve as one that is written in
+// the second pass or later).
 struct RadixSort {
     RadixArrays in, out, tmp;
     int64_t n;
     int bits;
 };
+// passes of a sort by `bits` bits; they write out and tmp in turn, the last one out
+int radix_passes(int bits);
 // uint32 words of scratch radix_sort needs for sorts of n0 and n1 keys
 size_t radix_scratch_words(int64_t n0, int64_t n1);
 // one or two such sorts (of the same number of arrays) in the same launches
@@ -303,8 +306,10 @@ hipError_t launch_edge_ids(const int32_t* out_eid, int32_t* pos, const int32_t* 
 // ones, 2 and 3 the same of the reverse CSR.
 constexpr int SUMMARY_DEG = 4096;  // the largest threshold the small-row option takes
 constexpr int SUMMARY_TABLES = 4;
+constexpr int SUMMARY_SAMPLES = 16384;
 struct BuildSummary {
     int32_t flag;
+    int32_t near_ids;                     // of SUMMARY_SAMPLES in-CSR positions: next id within 32 of theirs
     int32_t n_hub[SUMMARY_TABLES], n_seg[SUMMARY_TABLES];
     int32_t max_deg[2];
     int32_t above_far[2];                 // rows of more than SummaryArgs::far edges
@@ -316,7 +321,8 @@ struct SummaryArgs {
     int64_t n_edges;
     int64_t seg_edges[SUMMARY_TABLES];
     int64_t far[2];
-    BuildSummary* out;
+    const int32_t* eid;  // the in-CSR's edge ids, nullptr: identity
+    BuildSummary* out;   // its flag and near_ids zeroed beforehand
 };
 hipError_t launch_summary(const SummaryArgs& a, hipStream_t s);
 // the hub tables of a graph: offsets and segments (with the sort keys of the
