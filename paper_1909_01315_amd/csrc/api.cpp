@@ -1041,7 +1041,8 @@ gnnk_status gat_aggregate(gnnk_graph_t g, const gnnk_tensor* feat, const gnnk_te
     set_geo(A, geo);
     A.sch = schedule(g->in_nbr, geo, true);
     const int dt = dtype_code(out);
-    const size_t part = (size_t)A.sch.n_seg * 3 * geo.D * 8, ml = attn ? (size_t)A.sch.n_hub * 2 * geo.D * 8 : 0;
+    A.partial_stride = geo.D + 2 * H;  // a segment's weighted row and (max, sum) per head
+    const size_t part = (size_t)A.sch.n_seg * A.partial_stride * 8, ml = attn ? (size_t)A.sch.n_hub * 2 * geo.D * 8 : 0;
     void* row_ml = nullptr;
     if (part + ml > 0) {
         Scratch sc = scratch_of(g, stream);
@@ -1083,6 +1084,9 @@ static gnnk_status gat_bwd_run(gnnk_graph_t g, const gnnk_tensor* feat, const gn
     ain.csr = csr_of(g, g->in_nbr, false);
     set_geo(ain, geo);
     ain.sch = schedule(g->in_nbr, geo, true);
+    aout.a = operand(grad_out, ms[2].kind, T_NBR);
+    aout.x2 = rec;
+    aout.x2_stride = H;
     aout.csr = csr_of(g, g->out_fine_nbr, false);
     set_geo(aout, geo);
     aout.sch = schedule(g->out_fine_nbr, geo, true);
@@ -1116,7 +1120,8 @@ static gnnk_status gat_bwd_run(gnnk_graph_t g, const gnnk_tensor* feat, const gn
     B.acc_src = acc_src;
     const int es = dt == 1 ? 2 : 4;
     const bool fast = !options().no_fast && fast_geo(geo, dt) && fits32(ain.a, g->n_src, es) &&
-                      fits32(ain.b, g->n_src, es);
+                      fits32(ain.b, g->n_src, es) && fits32(aout.a, g->n_dst, es) &&
+                      (int64_t)H * 16 < (1 << 24) && (uint64_t)g->n_dst * H * 16 <= 0xFFFFFFFFull;
     return GNNK_LAUNCH(launch_gat_backward(ain, aout, B, dt, geo.vec, fast ? geo.G : 0, stream),
                          "fused attention backward launch");
 }

@@ -337,6 +337,7 @@ struct Raw {
     int32_t k[VEC];
     int32_t dg;
     uint32_t kb;  // EXT_BITS: the winner bits of this lane's VEC columns
+    float4 rec;   // EXT_REC: the record of the neighbour and the lane's head
 };
 
 // EXT_BITS: the winner bits of an edge (its CSR position) are read before
@@ -388,6 +389,14 @@ __device__ __forceinline__ void fetch(const EngineArgs& A, int32_t nb, int32_t e
     }
     const int32_t ar = row_of(S::AT == DYN ? A.a.target : S::AT, nb, ed, self);
     if constexpr (EXT == EXT_SCALE) r.dg = A.deg[ar];
+    if constexpr (EXT == EXT_REC) {
+        const float4* rec = reinterpret_cast<const float4*>(A.x2);
+        if constexpr (F)
+            r.rec = *reinterpret_cast<const float4*>(reinterpret_cast<const char*>(rec) +
+                                                     (__umul24((uint32_t)nb, (uint32_t)A.x2_stride * 16u) +
+                                                      (uint32_t)h * 16u));
+        else r.rec = rec[(int64_t)nb * A.x2_stride + h];
+    }
     if constexpr (EXT == EXT_MASK) {
         if constexpr (F) {
             const uint32_t off = __umul24((uint32_t)ar, (uint32_t)A.mask_ld * 4u) + (uint32_t)col0 * 4u;

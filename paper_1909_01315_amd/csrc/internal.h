@@ -116,6 +116,7 @@ enum : int {
     EXT_SCALE = 1,  // a / deg(row of a)
     EXT_MASK = 2,   // a where arg[row of a][col] == edge id
     EXT_BITS = 3,   // a where bit col of the winner mask at this CSR position is set
+    EXT_REC = 4,    // a as it is, with the float4 record x2[neighbour * x2_stride + head] loaded beside it
 };
 
 inline int ext_of(int32_t flags) {
