@@ -17,7 +17,7 @@ LIB = os.path.join(HERE, "libgnnk.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
 
-SOURCES = ["spmm.hip", "sddmm.hip", "edge.hip", "gat.hip", "softmax.hip", "misc.hip", "build.hip", "noalloc.hip",
+SOURCES = ["spmm.hip", "spmm_ov.hip", "sddmm.hip", "edge.hip", "gat.hip", "softmax.hip", "misc.hip", "build.hip", "noalloc.hip",
            "graph.cpp", "api.cpp"]
 
 COMMON = ["-O3", "-std=c++17", "-fPIC", "-Wall", "-I", os.path.join(ROOT, "include"), "-I", CSRC]

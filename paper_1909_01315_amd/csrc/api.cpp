@@ -38,6 +38,7 @@ struct Member {
 
 struct Geo {
     int H = 1, F = 1, vec = 1, NV = 1, L = 1, log2L = 0, G = 64, nchunk = 1;
+    int FV = 1, ov = 0;  // vectors per head, columns its last one shares with the one before
     bool merged = false;
     int64_t D = 1;
 };
@@ -53,8 +54,19 @@ int pow2ceil(int x) {
 // merge into one row of Hm * Fm columns, unless keep_heads (a kernel that
 // needs each lane's head, as the fused attention does; with Fm = 1 its
 // per-head scores have the shape of a full operand).
-gnnk_status choose_geo(int Hm, int Fm, std::vector<Member>& ms, const std::vector<const void*>& int_arrays, Geo& g,
-                       bool keep_heads = false) {
+//
+// Vectors: the widest of 8 (bf16), 4, 2 and 1 columns that divides F, at the
+// elements' own alignment.  Where that is less than four and overlap is
+// allowed, four (fp32) or eight (bf16), a head's
+// last vector overlapping the one before it: rows of 47 columns take 12 lanes
+// of 16 (bf16: 6 of 8) and the compile-time layouts instead of 47 of 64 and
+// the runtime ones.  8.4M edges from 262,144 nodes, 47 columns, mean forward
+// and backward: fp32 796 -> 730 us (bound by the lines its rows touch, 2.5 of
+// 128 bytes each), bf16 828 -> 507; the u_dot_v step 1862 -> 1284; 640,000
+// edges, 3 heads of 45, fused attention step 852 -> 172.  The choice depends
+// on F and the type alone, so every pass of a call makes the same one.
+gnnk_status choose_geo(int Hm, int Fm, std::vector<Member>& ms, Geo& g, bool keep_heads = false,
+                       bool overlap = true) {
     for (auto& m : ms) {
         m.kind = kind_of(m.t, Hm, Fm);
         if (m.kind == K_BAD)
@@ -68,24 +80,13 @@ gnnk_status choose_geo(int Hm, int Fm, std::vector<Member>& ms, const std::vecto
     g.F = g.merged ? Hm * Fm : Fm;
     g.D = (int64_t)Hm * Fm;
     const int es = ms.empty() ? 4 : (ms[0].t->dtype == GNNK_BF16 ? 2 : 4);
-    int cand[4] = {8, 4, 2, 1};
-    g.vec = 1;
-    for (int v : cand) {
-        if (v == 8 && es == 4) continue;
-        if (g.F % v) continue;
-        bool ok = true;
-        for (auto& m : ms) {
-            if (m.kind != K_FULL) continue;
-            if ((uintptr_t)m.t->data % (size_t)(v * es) || m.t->row_stride % v) ok = false;
-        }
-        for (const void* p : int_arrays)
-            if (p && (uintptr_t)p % (size_t)std::min(16, v * 4)) ok = false;
-        if (ok) {
-            g.vec = v;
-            break;
-        }
-    }
-    g.NV = (int)(g.D / g.vec);
+    g.vec = es == 2 && g.F % 8 == 0 ? 8 : (g.F % 4 == 0 ? 4 : (g.F % 2 == 0 ? 2 : 1));
+    // (the edge-parallel walks would add the shared columns twice)
+    const int wide = es == 2 ? 8 : 4;
+    if (overlap && g.vec < 4 && g.F >= wide && options().schedule < 2 && g.D <= 65536) g.vec = wide;
+    g.FV = (g.F + g.vec - 1) / g.vec;
+    g.ov = g.FV * g.vec - g.F;
+    g.NV = g.H * g.FV;
     if (g.NV > 64) {
         g.L = 64;
         g.nchunk = (g.NV + 63) / 64;
@@ -124,7 +125,7 @@ gnnk_status out_desc(const gnnk_tensor* t, Kind k, const Geo& g, OutDev& o) {
     if (k == K_HEADS && g.F != g.D) {
         // the entry points split the heads into slices of at most one pass
         if (g.nchunk > 1) return fail(GNNK_EUNSUPPORTED, "per-head sums wider than one pass of the wavefront");
-        o.red = g.F / g.vec;
+        o.red = g.FV;
         o.per_head = 1;
     } else {
         // the whole row: lanes past NV hold zeros, so a run of L lanes (a
@@ -187,6 +188,10 @@ void set_geo(EngineArgs& A, const Geo& g) {
     A.geo.log2L = g.log2L;
     A.geo.G = g.G;
     A.geo.nchunk = g.nchunk;
+    A.geo.FV = g.FV;
+    A.geo.ov = g.ov;
+    A.geo.D = (int32_t)g.D;
+    A.geo.fv_magic = (uint32_t)((0x80000000ull + (uint32_t)g.FV - 1) / (uint32_t)g.FV);
 }
 
 int dtype_code(const gnnk_tensor* t) { return t->dtype == GNNK_BF16 ? 1 : 0; }
@@ -269,7 +274,9 @@ Pick pick_spmm(const gnnk_graph* g, const Dir& d, EngineArgs& A, const Geo& geo,
 // the compile-time layout of a g-SDDMM call (walks the in-CSR)
 Pick pick_sddmm(const gnnk_graph* g, const EngineArgs& A, const Geo& geo, int dtype, int opk) {
     Pick p;
-    if (options().no_fast || !fast_geo(geo, dtype) || ext_of(A.flags) != EXT_NONE || opk == 0) return p;
+    // overlapping vectors: the runtime layouts (a test per edge in the fast
+    // kernels' sums took c3's u_dot_v from 3.26 to 3.43 ms)
+    if (options().no_fast || !fast_geo(geo, dtype) || ext_of(A.flags) != EXT_NONE || opk == 0 || geo.ov) return p;
     if (!A.a.full || !A.b.full) return p;
     // reduced outputs need power-of-two runs of lanes (DPP sums) within one
     // pass of the wavefront
@@ -328,7 +335,7 @@ gnnk_status run_spmm_sum(gnnk_graph* g, const Dir& d, EngineArgs& A, const Geo& 
     if (fused_dw) {
         const int r2 = A.red2;
         *fused_dw = walk == 0 && (pk.spec == SP_UE_H || pk.spec == SP_UE_R) &&
-                    (pk.gc == 1 || pk.gc == 2 || pk.gc == 4) && geo.nchunk == 1 && r2 >= 1 &&
+                    (pk.gc == 1 || pk.gc == 2 || pk.gc == 4) && geo.nchunk == 1 && geo.ov == 0 && r2 >= 1 &&
                     (r2 & (r2 - 1)) == 0 && r2 <= geo.L;
     }
     if (walk) {
@@ -426,9 +433,10 @@ gnnk_tensor head_slice(const gnnk_tensor* t, int Hm, int h0, int hc) {
 // per head of an (Hm, Fm) message, Fm > 1) that would need more than one pass
 // of the wavefront: Fm / vec lanes per head, 64 lanes per pass; one head per
 // slice when a head alone is wider (its sum then runs over several passes).
-// 0: the call runs whole.
+// 0: the call runs whole.  overlap: whether every pass of the call may overlap
+// vectors.
 int heads_per_slice(int Hm, int Fm, std::initializer_list<const gnnk_tensor*> all,
-                    std::initializer_list<const gnnk_tensor*> outs, const void* int_array = nullptr) {
+                    std::initializer_list<const gnnk_tensor*> outs, bool overlap = true) {
     if (Hm <= 1 || Fm <= 1) return 0;
     bool per_head = false;
     for (const gnnk_tensor* t : outs)
@@ -438,8 +446,8 @@ int heads_per_slice(int Hm, int Fm, std::initializer_list<const gnnk_tensor*> al
     for (const gnnk_tensor* t : all)
         if (t) ms.push_back({t, K_FULL});
     Geo geo;
-    if (choose_geo(Hm, Fm, ms, {int_array}, geo) != GNNK_OK || geo.merged || geo.nchunk == 1) return 0;
-    return std::max(1, 64 / (Fm / geo.vec));
+    if (choose_geo(Hm, Fm, ms, geo, false, overlap) != GNNK_OK || geo.merged || geo.nchunk == 1) return 0;
+    return std::max(1, 64 / geo.FV);
 }
 
 }  // namespace
@@ -473,7 +481,7 @@ gnnk_status gspmm_impl(gnnk_graph_t g, gnnk_binop op, gnnk_reduce reduce, const 
     if (use_r) ms.push_back({rhs, K_FULL});
     ms.push_back({out, K_FULL});
     Geo geo;
-    gnnk_status st = choose_geo(Hm, Fm, ms, {arg_lhs, arg_rhs}, geo);
+    gnnk_status st = choose_geo(Hm, Fm, ms, geo);
     if (st != GNNK_OK) return st;
     if (g->n_dst == 0) return GNNK_OK;
     EngineArgs A{};
@@ -624,7 +632,7 @@ gnnk_status gsddmm(gnnk_graph_t g, gnnk_binop op, const gnnk_tensor* lhs, gnnk_t
     if (use_r) ms.push_back({rhs, K_FULL});
     ms.push_back({out, K_FULL});
     Geo geo;
-    gnnk_status st = choose_geo(Hm, Fm, ms, {}, geo);
+    gnnk_status st = choose_geo(Hm, Fm, ms, geo);
     if (st != GNNK_OK) return st;
     if (g->n_edges == 0) return GNNK_OK;
     EngineArgs A{};
@@ -676,7 +684,7 @@ static gnnk_status spmm_backward(gnnk_graph_t g, gnnk_binop op, gnnk_reduce redu
     if (grad_rhs && (grad_rhs->rows != g->n_edges || grad_rhs->heads != rhs->heads || grad_rhs->feat != rhs->feat))
         return fail(GNNK_EINVAL, "grad_rhs must have rhs's shape");
     const int64_t ld = arg_ld >= 0 ? arg_ld : (int64_t)Hm * Fm;
-    if (const int hs = heads_per_slice(Hm, Fm, {lhs, rhs, grad_out, grad_lhs, grad_rhs}, {grad_lhs, grad_rhs}, arg_rhs)) {
+    if (const int hs = heads_per_slice(Hm, Fm, {lhs, rhs, grad_out, grad_lhs, grad_rhs}, {grad_lhs, grad_rhs}, !cmp)) {
         // per-head gradients wider than one pass: slices of heads, one call each
         for (int h0 = 0; h0 < Hm; h0 += hs) {
             const int hc = std::min(hs, Hm - h0);
@@ -703,7 +711,11 @@ static gnnk_status spmm_backward(gnnk_graph_t g, gnnk_binop op, gnnk_reduce redu
         if (op == GNNK_MUL || op == GNNK_DIV) ms.push_back({rhs, K_FULL});
         ms.push_back({grad_lhs, K_FULL});
         Geo geo;
-        gnnk_status st = choose_geo(Hm, Fm, ms, {arg_rhs}, geo);
+        gnnk_status st = choose_geo(Hm, Fm, ms, geo);
+        // winner masks: a vector's bits lie in one 32-bit word, so no overlap
+        // of heads' vectors, nor of a row's last one into the word before
+        if (st == GNNK_OK && cmp && geo.ov && (!geo.merged || (geo.D % 32 != 0 && geo.D % 32 < geo.vec)))
+            st = choose_geo(Hm, Fm, ms, geo, false, false);
         if (st != GNNK_OK) return st;
         EngineArgs A{};
         A.a = operand(grad_out, ms[0].kind, T_NBR);
@@ -782,7 +794,7 @@ static gnnk_status spmm_backward(gnnk_graph_t g, gnnk_binop op, gnnk_reduce redu
             A.out2 = grad_rhs->data;
             A.out2_stride = grad_rhs->row_stride;
             A.per_head2 = rhs->heads > 1 ? 1 : 0;
-            A.red2 = A.per_head2 ? Fm / geo.vec : (int32_t)geo.NV;
+            A.red2 = A.per_head2 ? geo.FV : (int32_t)geo.NV;
         }
         // node rows gathered in the finer segments; the argmax scatter, which
         // reads its masks in order and gathers few rows, keeps the coarse ones
@@ -796,7 +808,7 @@ static gnnk_status spmm_backward(gnnk_graph_t g, gnnk_binop op, gnnk_reduce redu
         if (op == GNNK_DIV) ms.push_back({rhs, K_FULL});
         ms.push_back({grad_rhs, K_FULL});
         Geo geo;
-        gnnk_status st = choose_geo(Hm, Fm, ms, {arg_rhs}, geo);
+        gnnk_status st = choose_geo(Hm, Fm, ms, geo);
         if (st != GNNK_OK) return st;
         EngineArgs A{};
         A.a = operand(grad_out, ms[0].kind, T_SELF);
@@ -926,7 +938,7 @@ static gnnk_status sddmm_backward(gnnk_graph_t g, gnnk_binop op, const gnnk_tens
         if (ct) ms.push_back({ct, K_FULL});
         ms.push_back({gx, K_FULL});
         Geo geo;
-        gnnk_status st = choose_geo(Hm, Fm, ms, {}, geo);
+        gnnk_status st = choose_geo(Hm, Fm, ms, geo);
         if (st != GNNK_OK) return st;
         if (swap) {
             A.a = operand(bt, ms[0].kind, tg(b_target));
@@ -973,7 +985,7 @@ static gnnk_status softmax_common(gnnk_graph_t g, const gnnk_tensor* a, const gn
     std::vector<Member> ms{{a, K_FULL}, {out, K_FULL}};
     if (b) ms.push_back({b, K_FULL});
     Geo geo;
-    gnnk_status st = choose_geo(a->heads, a->feat, ms, {}, geo);
+    gnnk_status st = choose_geo(a->heads, a->feat, ms, geo, false, false);
     if (st != GNNK_OK) return st;
     if (g->n_edges == 0) return GNNK_OK;
     EngineArgs A{};
@@ -1027,7 +1039,7 @@ gnnk_status gat_aggregate(gnnk_graph_t g, const gnnk_tensor* feat, const gnnk_te
     // el and er broadcast over features: keep heads separate (F per head)
     std::vector<Member> ms{{feat, K_FULL}, {el, K_FULL}, {out, K_FULL}};
     Geo geo;
-    gnnk_status st = choose_geo(H, F, ms, {}, geo, true);
+    gnnk_status st = choose_geo(H, F, ms, geo, true);
     if (st != GNNK_OK) return st;
     if (g->n_dst == 0) return GNNK_OK;
     EngineArgs A{};
@@ -1073,7 +1085,7 @@ static gnnk_status gat_bwd_run(gnnk_graph_t g, const gnnk_tensor* feat, const gn
     const int H = feat->heads, F = feat->feat;
     std::vector<Member> ms{{feat, K_FULL}, {el, K_FULL}, {grad_out, K_FULL}};
     Geo geo;
-    gnnk_status st = choose_geo(H, F, ms, {}, geo, true);
+    gnnk_status st = choose_geo(H, F, ms, geo, true);
     if (st != GNNK_OK) return st;
     if (geo.nchunk != 1) return fail(GNNK_EUNSUPPORTED, "fused attention backward: a slice wider than one pass");
     const int dt = dtype_code(grad_out);
@@ -1160,7 +1172,7 @@ static gnnk_status gat_backward(gnnk_graph_t g, const gnnk_tensor* feat, const g
         return fail(GNNK_EINVAL, "each gradient must have its operand's shape");
     std::vector<Member> ms{{feat, K_FULL}, {el, K_FULL}, {grad_out, K_FULL}};
     Geo geo;
-    gnnk_status st = choose_geo(H, F, ms, {}, geo, true);
+    gnnk_status st = choose_geo(H, F, ms, geo, true);
     if (st != GNNK_OK) return st;
     Scratch sc = scratch_of(g, stream);
     if (geo.nchunk == 1) {
@@ -1172,7 +1184,7 @@ static gnnk_status gat_backward(gnnk_graph_t g, const gnnk_tensor* feat, const g
     // a head's dot products are reduced across the lanes of one pass: rows
     // wider than a pass run as slices of heads (heads are independent), and
     // a head wider than a pass in column chunks of one pass each
-    const int lanes = F / geo.vec;
+    const int lanes = geo.FV;
     const int hs = lanes <= 64 ? 64 / lanes : 1;
     const int cw = lanes <= 64 ? F : 64 * geo.vec;
     const int nc = (F + cw - 1) / cw;

@@ -36,14 +36,34 @@ __device__ __forceinline__ uint32_t f2bf(float f) {
 template <typename T, int VEC>
 struct IO;
 
+// Vectors are read and written at the alignment of their elements: the
+// hardware takes 8- and 16-byte accesses of global memory at any address, so
+// rows of odd widths and strides take as wide loads as any other.
+typedef float f4_el __attribute__((ext_vector_type(4), aligned(4)));
+typedef float f2_el __attribute__((ext_vector_type(2), aligned(4)));
+typedef int i4_el __attribute__((ext_vector_type(4), aligned(4)));
+typedef int i2_el __attribute__((ext_vector_type(2), aligned(4)));
+typedef unsigned u4_h __attribute__((ext_vector_type(4), aligned(2)));
+typedef unsigned u2_h __attribute__((ext_vector_type(2), aligned(2)));
+typedef unsigned u1_h __attribute__((aligned(2)));
+// (plain accesses go through these structs, which become the same wide
+// accesses: of two branches that differ only in the nontemporal hint the
+// compiler otherwise makes one without it, which cost the softmax passes 8%)
+struct F4 {
+    float x, y, z, w;
+};
+struct I4 {
+    int x, y, z, w;
+};
+
 template <int VEC>
 struct IO<float, VEC> {
     static __device__ __forceinline__ void load(const float* p, float* v) {
         if constexpr (VEC == 4) {
-            float4 x = *reinterpret_cast<const float4*>(p);
+            const F4 x = *reinterpret_cast<const F4*>(p);
             v[0] = x.x; v[1] = x.y; v[2] = x.z; v[3] = x.w;
         } else if constexpr (VEC == 2) {
-            float2 x = *reinterpret_cast<const float2*>(p);
+            const f2_el x = *reinterpret_cast<const f2_el*>(p);
             v[0] = x.x; v[1] = x.y;
         } else {
             v[0] = *p;
@@ -51,13 +71,11 @@ struct IO<float, VEC> {
     }
     static __device__ __forceinline__ float load1(const float* p) { return *p; }
     static __device__ __forceinline__ void load_nt(const float* p, float* v) {
-        typedef float f4 __attribute__((ext_vector_type(4)));
-        typedef float f2 __attribute__((ext_vector_type(2)));
         if constexpr (VEC == 4) {
-            f4 x = __builtin_nontemporal_load(reinterpret_cast<const f4*>(p));
+            const f4_el x = __builtin_nontemporal_load(reinterpret_cast<const f4_el*>(p));
             v[0] = x.x; v[1] = x.y; v[2] = x.z; v[3] = x.w;
         } else if constexpr (VEC == 2) {
-            f2 x = __builtin_nontemporal_load(reinterpret_cast<const f2*>(p));
+            const f2_el x = __builtin_nontemporal_load(reinterpret_cast<const f2_el*>(p));
             v[0] = x.x; v[1] = x.y;
         } else {
             v[0] = __builtin_nontemporal_load(p);
@@ -66,9 +84,10 @@ struct IO<float, VEC> {
     static __device__ __forceinline__ float load1_nt(const float* p) { return __builtin_nontemporal_load(p); }
     static __device__ __forceinline__ void store(float* p, const float* v) {
         if constexpr (VEC == 4) {
-            *reinterpret_cast<float4*>(p) = make_float4(v[0], v[1], v[2], v[3]);
+            *reinterpret_cast<F4*>(p) = F4{v[0], v[1], v[2], v[3]};
         } else if constexpr (VEC == 2) {
-            *reinterpret_cast<float2*>(p) = make_float2(v[0], v[1]);
+            const f2_el x = {v[0], v[1]};
+            *reinterpret_cast<f2_el*>(p) = x;
         } else {
             *p = v[0];
         }
@@ -78,10 +97,9 @@ struct IO<float, VEC> {
     // partial-line writes that L2 does not merge (a g-SDDMM with one value
     // per edge ran twice as long with them); those stay plain
     static __device__ __forceinline__ void store_nt(float* p, const float* v) {
-        typedef float f4 __attribute__((ext_vector_type(4)));
         if constexpr (VEC == 4) {
-            f4 x = {v[0], v[1], v[2], v[3]};
-            __builtin_nontemporal_store(x, reinterpret_cast<f4*>(p));
+            const f4_el x = {v[0], v[1], v[2], v[3]};
+            __builtin_nontemporal_store(x, reinterpret_cast<f4_el*>(p));
         } else {
             store(p, v);
         }
@@ -94,14 +112,14 @@ template <int VEC>
 struct IO<bf16_t, VEC> {
     static __device__ __forceinline__ void load(const bf16_t* p, float* v) {
         if constexpr (VEC == 8) {
-            uint4 x = *reinterpret_cast<const uint4*>(p);
+            const u4_h x = *reinterpret_cast<const u4_h*>(p);
             v[0] = bf_lo(x.x); v[1] = bf_hi(x.x); v[2] = bf_lo(x.y); v[3] = bf_hi(x.y);
             v[4] = bf_lo(x.z); v[5] = bf_hi(x.z); v[6] = bf_lo(x.w); v[7] = bf_hi(x.w);
         } else if constexpr (VEC == 4) {
-            uint2 x = *reinterpret_cast<const uint2*>(p);
+            const u2_h x = *reinterpret_cast<const u2_h*>(p);
             v[0] = bf_lo(x.x); v[1] = bf_hi(x.x); v[2] = bf_lo(x.y); v[3] = bf_hi(x.y);
         } else if constexpr (VEC == 2) {
-            uint32_t x = *reinterpret_cast<const uint32_t*>(p);
+            const uint32_t x = *reinterpret_cast<const u1_h*>(p);
             v[0] = bf_lo(x); v[1] = bf_hi(x);
         } else {
             v[0] = bf_lo(*p);
@@ -110,29 +128,25 @@ struct IO<bf16_t, VEC> {
     static __device__ __forceinline__ float load1(const bf16_t* p) { return bf_lo(*p); }
     static __device__ __forceinline__ void load_nt(const bf16_t* p, float* v) { load(p, v); }
     static __device__ __forceinline__ float load1_nt(const bf16_t* p) { return load1(p); }
+    static __device__ __forceinline__ uint32_t two(float a, float b) { return f2bf(a) | (f2bf(b) << 16); }
     static __device__ __forceinline__ void store(bf16_t* p, const float* v) {
         if constexpr (VEC == 8) {
-            uint4 x;
-            x.x = f2bf(v[0]) | (f2bf(v[1]) << 16); x.y = f2bf(v[2]) | (f2bf(v[3]) << 16);
-            x.z = f2bf(v[4]) | (f2bf(v[5]) << 16); x.w = f2bf(v[6]) | (f2bf(v[7]) << 16);
-            *reinterpret_cast<uint4*>(p) = x;
+            const u4_h x = {two(v[0], v[1]), two(v[2], v[3]), two(v[4], v[5]), two(v[6], v[7])};
+            *reinterpret_cast<u4_h*>(p) = x;
         } else if constexpr (VEC == 4) {
-            uint2 x;
-            x.x = f2bf(v[0]) | (f2bf(v[1]) << 16); x.y = f2bf(v[2]) | (f2bf(v[3]) << 16);
-            *reinterpret_cast<uint2*>(p) = x;
+            const u2_h x = {two(v[0], v[1]), two(v[2], v[3])};
+            *reinterpret_cast<u2_h*>(p) = x;
         } else if constexpr (VEC == 2) {
-            *reinterpret_cast<uint32_t*>(p) = f2bf(v[0]) | (f2bf(v[1]) << 16);
+            *reinterpret_cast<u1_h*>(p) = two(v[0], v[1]);
         } else {
             *p = (bf16_t)f2bf(v[0]);
         }
     }
     static __device__ __forceinline__ void store1(bf16_t* p, float v) { *p = (bf16_t)f2bf(v); }
     static __device__ __forceinline__ void store_nt(bf16_t* p, const float* v) {
-        typedef unsigned u4 __attribute__((ext_vector_type(4)));
         if constexpr (VEC == 8) {
-            u4 x = {f2bf(v[0]) | (f2bf(v[1]) << 16), f2bf(v[2]) | (f2bf(v[3]) << 16), f2bf(v[4]) | (f2bf(v[5]) << 16),
-                    f2bf(v[6]) | (f2bf(v[7]) << 16)};
-            __builtin_nontemporal_store(x, reinterpret_cast<u4*>(p));
+            const u4_h x = {two(v[0], v[1]), two(v[2], v[3]), two(v[4], v[5]), two(v[6], v[7])};
+            __builtin_nontemporal_store(x, reinterpret_cast<u4_h*>(p));
         } else {
             store(p, v);
         }
@@ -147,11 +161,11 @@ __device__ __forceinline__ void load_i32(const int32_t* p, int32_t* v) {
     if constexpr (VEC >= 4 && VEC % 4 == 0) {
 #pragma unroll
         for (int q = 0; q < VEC / 4; ++q) {
-            int4 x = reinterpret_cast<const int4*>(p)[q];
+            const i4_el x = reinterpret_cast<const i4_el*>(p)[q];
             v[4 * q] = x.x; v[4 * q + 1] = x.y; v[4 * q + 2] = x.z; v[4 * q + 3] = x.w;
         }
     } else if constexpr (VEC == 2) {
-        int2 x = *reinterpret_cast<const int2*>(p);
+        const i2_el x = *reinterpret_cast<const i2_el*>(p);
         v[0] = x.x; v[1] = x.y;
     } else {
         v[0] = *p;
@@ -162,19 +176,16 @@ __device__ __forceinline__ void load_i32(const int32_t* p, int32_t* v) {
 // vectors when NT (narrower ones stay plain, as in IO::store_nt)
 template <int VEC, bool NT = true>
 __device__ __forceinline__ void store_i32(int32_t* p, const int32_t* v) {
-    typedef int i4 __attribute__((ext_vector_type(4)));
-    if constexpr (NT && VEC >= 4 && VEC % 4 == 0) {
+    if constexpr (VEC >= 4 && VEC % 4 == 0) {
 #pragma unroll
         for (int q = 0; q < VEC / 4; ++q) {
-            i4 x = {v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]};
-            __builtin_nontemporal_store(x, reinterpret_cast<i4*>(p) + q);
+            const i4_el x = {v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]};
+            if constexpr (NT) __builtin_nontemporal_store(x, reinterpret_cast<i4_el*>(p) + q);
+            else reinterpret_cast<I4*>(p)[q] = I4{x.x, x.y, x.z, x.w};
         }
-    } else if constexpr (VEC >= 4 && VEC % 4 == 0) {
-#pragma unroll
-        for (int q = 0; q < VEC / 4; ++q)
-            reinterpret_cast<int4*>(p)[q] = make_int4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
     } else if constexpr (VEC == 2) {
-        *reinterpret_cast<int2*>(p) = make_int2(v[0], v[1]);
+        const i2_el x = {v[0], v[1]};
+        *reinterpret_cast<i2_el*>(p) = x;
     } else {
         *p = v[0];
     }
@@ -267,17 +278,22 @@ __device__ __forceinline__ double seg_sum(double v, int lane_in_group, int red) 
 enum : int { DYN = -1 };
 enum : int { OK_FULL = 0, OK_HEAD = 1, OK_ROW = 2 };
 
-template <int AT_, int AK_, int BT_, int BK_, int GC_, bool CB_, bool PRE_ = true>
+template <int AT_, int AK_, int BT_, int BK_, int GC_, bool CB_, bool PRE_ = true, bool OV_ = false>
 struct Spec {
     static constexpr int AT = AT_, AK = AK_, BT = BT_, BK = BK_;
     static constexpr int GC = GC_;    // lane groups per wavefront, 0 = runtime (no scalar id batches)
     static constexpr bool CB = CB_;   // b is read with one coalesced load per batch (identity edge ids)
     static constexpr bool FAST = GC_ > 0;
+    // a head's last vector overlaps the one before it (kernels of their own:
+    // the column arithmetic at run time cost the others 0.5-4%)
+    static constexpr bool OV = OV_;
     // an operand on the row itself is loaded once per row (false: per edge,
     // as in edge-parallel walks where consecutive edges change rows)
     static constexpr bool PRE = PRE_ && FAST;
 };
-using SpecDyn = Spec<DYN, DYN, DYN, DYN, 0, false>;
+template <bool OV>
+using SpecDynT = Spec<DYN, DYN, DYN, DYN, 0, false, true, OV>;
+using SpecDyn = SpecDynT<false>;
 
 __device__ __forceinline__ int32_t row_of(int32_t target, int32_t nb, int32_t ed, int32_t self) {
     return target == T_NBR ? nb : (target == T_EDGE ? ed : self);
@@ -346,6 +362,7 @@ template <int VEC, int EXT>
 __device__ __forceinline__ void fetch_bits(const EngineArgs& A, int32_t pos, int col0, Raw<VEC>& r) {
     if constexpr (EXT == EXT_BITS) {
         const uint32_t* M = reinterpret_cast<const uint32_t*>(A.mask_arg);
+        // (the host overlaps no vectors across two words)
         const uint32_t w = M[(uint64_t)(uint32_t)pos * (uint32_t)A.mask_ld + (uint32_t)(col0 >> 5)];
         r.kb = (w >> (col0 & 31)) & ((VEC == 32 ? 0u : (1u << VEC)) - 1u);
     }
@@ -526,12 +543,28 @@ __device__ __forceinline__ bool better(float m, int32_t e, float best, int32_t b
 // ---------------------------------------------------------------------------
 // output of one reduced row (sums)
 
+// Columns of vector j of a message row (vector 0 for a lane outside it): the
+// first one, its head, and how many of them the vector before holds too.
+struct Cols {
+    int col0, h, skip;
+};
+template <int VEC, bool OV>
+__device__ __forceinline__ Cols cols_of(const GeomDev& geo, bool active, int j) {
+    j = active ? j : 0;
+    if constexpr (!OV) return Cols{j * VEC, j * VEC / geo.F, 0};
+    // h = j / FV: a multiplication (rows of overlapping vectors have at most
+    // 2^14 of them)
+    const int h = (int)__umulhi(2u * (uint32_t)j + 1u, geo.fv_magic);
+    const int at = j * VEC - h * geo.ov, last = h * geo.F + geo.F - VEC;
+    return Cols{at < last ? at : last, h, at > last ? geo.ov : 0};
+}
+
 // A reduced output of a row wider than one pass of the wavefront (nchunk > 1,
 // so one lane group of 64 lanes, whole-row sums only) adds each pass's total
 // into *carry (lane 0) and is written after the last pass; ch is the pass.
 template <typename T, int VEC>
 __device__ __forceinline__ void write_sum_row(const EngineArgs& A, int64_t row, bool active, int lig, int col0,
-                                              int h, double* acc, int64_t deg, bool write_lane,
+                                              int h, int skip, double* acc, int64_t deg, bool write_lane,
                                               bool may_reduce = true, int ch = 0, double* carry = nullptr) {
     if (A.flags & F_OWN_MEAN) {
         const double d = deg > 0 ? (double)deg : 1.0;
@@ -552,7 +585,7 @@ __device__ __forceinline__ void write_sum_row(const EngineArgs& A, int64_t row, 
     } else {
         double s = 0.0;
 #pragma unroll
-        for (int i = 0; i < VEC; ++i) s += acc[i];
+        for (int i = 0; i < VEC; ++i) s += i < skip ? 0.0 : acc[i];
         s = seg_sum(active ? s : 0.0, lig, A.out.red);
         if (A.geo.nchunk > 1 && carry) {
             *carry += s;

@@ -127,7 +127,7 @@ template <typename T, int VEC>
 __device__ __forceinline__ void gat_write_attn(const EngineArgs& A, const GatArgs& G, int64_t b64, int64_t e64,
                                                int64_t start, int stride, int lig, int h, bool active, float er_h,
                                                float m, double l) {
-    const int per_head = A.geo.F / VEC;  // lanes of one head
+    const int per_head = A.geo.FV;  // lanes of one head
     const bool writer = active & (lig % per_head == 0);
     const int32_t b = (int32_t)b64, e = (int32_t)e64;
     const T* el = reinterpret_cast<const T*>(A.b.data);
@@ -159,7 +159,7 @@ __global__ __launch_bounds__(256) void gat_kernel(EngineArgs A, GatArgs G) {
     const Lanes ln = lanes_of<S::GC>(geo);
     const int Gn = S::GC > 0 ? S::GC : geo.G;
     const int L = WAVE / Gn;
-    const int64_t D = (int64_t)geo.NV * VEC;
+    const int64_t D = (int64_t)geo.D;
 
     if (w < A.sch.w_big_end) {
         int64_t r, b, e;
@@ -177,8 +177,8 @@ __global__ __launch_bounds__(256) void gat_kernel(EngineArgs A, GatArgs G) {
         for (int ch = 0; ch < geo.nchunk; ++ch) {
             const int j = ch * L + ln.lig;
             const bool active = j < geo.NV;
-            const int col0 = active ? j * VEC : 0;
-            const int h = col0 / geo.F;
+            const Cols cc = cols_of<VEC, S::OV>(geo, active, j);
+            const int col0 = cc.col0, h = cc.h;
             const float er_h = load_er<T, VEC>(G, (int32_t)r, h);
             Online<VEC> st;
             st.init();
@@ -224,8 +224,8 @@ __global__ __launch_bounds__(256) void gat_kernel(EngineArgs A, GatArgs G) {
         for (int ch = 0; ch < geo.nchunk; ++ch) {
             const int j = ch * L + ln.lig;
             const bool active = j < geo.NV;
-            const int col0 = active ? j * VEC : 0;
-            const int h = col0 / geo.F;
+            const Cols cc = cols_of<VEC, S::OV>(geo, active, j);
+            const int col0 = cc.col0, h = cc.h;
             const float er_h = r >= 0 ? load_er<T, VEC>(G, self, h) : 0.0f;
             Online<VEC> st;
             st.init();
@@ -252,11 +252,12 @@ __global__ __launch_bounds__(256) void gat_kernel(EngineArgs A, GatArgs G) {
             for (int ch = 0; ch < geo.nchunk; ++ch) {
                 const int j = ch * L + ln.lig;
                 if (j < geo.NV && r >= 0) {
+                    const Cols cc = cols_of<VEC, S::OV>(geo, true, j);
                     float v[VEC];
 #pragma unroll
                     for (int i = 0; i < VEC; ++i) v[i] = 0.0f;
-                    IO<T, VEC>::store(reinterpret_cast<T*>(A.out.data) + r * A.out.stride + j * VEC, v);
-                    if ((j * VEC) % geo.F == 0) gat_write_stats(G, r, (j * VEC) / geo.F, 0.0f, 0.0);
+                    IO<T, VEC>::store(reinterpret_cast<T*>(A.out.data) + r * A.out.stride + cc.col0, v);
+                    if (j % geo.FV == 0) gat_write_stats(G, r, cc.h, 0.0f, 0.0);
                 }
             }
         }
@@ -267,7 +268,7 @@ __global__ __launch_bounds__(256) void gat_kernel(EngineArgs A, GatArgs G) {
 // row's final (m, sum) for the attention writes
 constexpr int GC_UNR = 4;
 
-template <typename T, int VEC>
+template <typename T, int VEC, bool OV>
 __global__ __launch_bounds__(256) void gat_combine_kernel(EngineArgs A, GatArgs G) {
     const int w = wave_id();
     const GeomDev& geo = A.geo;
@@ -278,16 +279,16 @@ __global__ __launch_bounds__(256) void gat_combine_kernel(EngineArgs A, GatArgs 
     const int64_t r = row_ok ? A.csr.perm[k] : -1;
     const int s0 = row_ok ? A.csr.hub_off[k] : 0;
     const int s1 = row_ok ? A.csr.hub_off[k + 1] : 0;
-    const int64_t D = (int64_t)geo.NV * VEC;
+    const int64_t D = (int64_t)geo.D;
     const double* P = reinterpret_cast<const double*>(A.partial);
     for (int ch = 0; ch < geo.nchunk; ++ch) {
         const int j = ch * geo.L + ln.lig;
         const bool active = j < geo.NV && row_ok;
-        const int col0 = active ? j * VEC : 0;
+        const Cols cc = cols_of<VEC, OV>(geo, active, j);
+        const int col0 = cc.col0, h = cc.h;
         if (!active) continue;
         // the row's maximum first, then its segments' sums against it, in
         // segment order; GC_UNR segments' loads in flight at once
-        const int h = col0 / geo.F;
         Online<VEC> st;
         st.init();
         const double* Q = P + (int64_t)s0 * A.partial_stride;
@@ -320,7 +321,7 @@ __global__ __launch_bounds__(256) void gat_combine_kernel(EngineArgs A, GatArgs 
 #pragma unroll
         for (int i = 0; i < VEC; ++i) v[i] = (float)(st.acc[i] / st.l);
         IO<T, VEC>::store(reinterpret_cast<T*>(A.out.data) + r * A.out.stride + col0, v);
-        if (col0 % geo.F == 0) gat_write_stats(G, r, col0 / geo.F, st.m, st.l);
+        if (col0 % geo.F == 0) gat_write_stats(G, r, h, st.m, st.l);
         if (G.attn) {
             double* ML = reinterpret_cast<double*>(G.row_ml) + k * 2 * D;
 #pragma unroll
@@ -333,20 +334,20 @@ __global__ __launch_bounds__(256) void gat_combine_kernel(EngineArgs A, GatArgs 
 }
 
 // hub rows with attention out: each segment writes its edges' a_e
-template <typename T, int VEC>
+template <typename T, int VEC, bool OV>
 __global__ __launch_bounds__(256) void gat_attn_segments_kernel(EngineArgs A, GatArgs G) {
     const int w = wave_id();
     if (w >= A.sch.n_seg) return;
     const GeomDev& geo = A.geo;
     const Lanes ln = lanes_of(geo);
-    const int64_t D = (int64_t)geo.NV * VEC;
+    const int64_t D = (int64_t)geo.D;
     const int4 sg = A.csr.seg[A.csr.seg_order[w]];
     const double* ML = reinterpret_cast<const double*>(G.row_ml) + (int64_t)sg.w * 2 * D;
     for (int ch = 0; ch < geo.nchunk; ++ch) {
         const int j = ch * geo.L + ln.lig;
         const bool active = j < geo.NV;
-        const int col0 = active ? j * VEC : 0;
-        const int h = col0 / geo.F;
+        const Cols cc = cols_of<VEC, OV>(geo, active, j);
+        const int col0 = cc.col0, h = cc.h;
         const float er_h = load_er<T, VEC>(G, sg.x, h);
         gat_write_attn<T, VEC>(A, G, sg.y, sg.z, ln.g, geo.G, ln.lig, h, active, er_h, (float)ML[col0],
                                ML[D + col0]);
@@ -381,6 +382,15 @@ __global__ __launch_bounds__(256) void gat_attn_segments_kernel(EngineArgs A, Ga
 // the lane group); the total is exact in the head's first lane
 __device__ __forceinline__ double head_sum(double v, int lig, int red) {
     return (red & (red - 1)) == 0 ? run_sum(v, red) : seg_sum(v, lig, red);
+}
+
+// a lane's share of a head's dot product without the first `skip` columns
+template <int VEC>
+__device__ __forceinline__ double last_share(const float (&x)[VEC], const double (&y)[VEC], int skip) {
+    double dp = 0.0;
+#pragma unroll
+    for (int i = 0; i < VEC; ++i) dp += i < skip ? 0.0 : (double)x[i] * y[i];
+    return dp;
 }
 
 // the attention of one edge, recomputed as the forward computes it
@@ -418,10 +428,10 @@ __device__ __forceinline__ void gat_bwd_dst_row(const EngineArgs& A, const GatBw
                                                 int64_t r, int64_t b, int64_t e, int slot) {
     const GeomDev& geo = A.geo;
     const int L = WAVE / Gn;
-    const int red = geo.F / VEC;  // lanes of a head
+    const int red = geo.FV;  // lanes of a head
     const bool active = ln.lig < geo.NV;
-    const int col0 = active ? ln.lig * VEC : 0;
-    const int h = col0 / geo.F;
+    const Cols cc = cols_of<VEC, S::OV>(geo, active, ln.lig);
+    const int col0 = cc.col0, h = cc.h;
     const bool head_lane = active && (col0 % geo.F) == 0;
     const int32_t self = r >= 0 ? (int32_t)r : 0;
     float dz[VEC];
@@ -442,6 +452,7 @@ __device__ __forceinline__ void gat_bwd_dst_row(const EngineArgs& A, const GatBw
         double dp = 0.0;
 #pragma unroll
         for (int i = 0; i < VEC; ++i) dp = fma((double)rw.a[i], dzd[i], dp);
+        if constexpr (S::OV) dp = last_share(rw.a, dzd, cc.skip);
         sS = fma(a, dp, sS);   // this lane's share of S and P
         sP = fma(al, dp, sP);
         sQ += al;              // the same in every lane of a head
@@ -501,13 +512,12 @@ __global__ __launch_bounds__(256) void gat_bwd_dst_kernel(EngineArgs A, GatBwdAr
     } else if (B.d_er) {
         // rows without in-edges: d_er = 0 (no edge reads their record)
         const int64_t k0 = A.sch.n_nz + ((int64_t)(w - A.sch.w_small_end) * Gn + ln.g) * A.sch.fill_rows_per_group;
-        const int col0 = ln.lig * VEC;
-        if (ln.lig < geo.NV && col0 % geo.F == 0) {
+        if (ln.lig < geo.NV && ln.lig % geo.FV == 0) {
             for (int q = 0; q < A.sch.fill_rows_per_group; ++q) {
                 const int64_t k = k0 + q;
                 if (k < A.sch.n_rows)
                     IO<T, 1>::store1(reinterpret_cast<T*>(B.d_er) + (int64_t)A.csr.perm[k] * B.d_er_stride +
-                                         col0 / geo.F, 0.0f);
+                                         ln.lig / geo.FV, 0.0f);
             }
         }
     }
@@ -575,10 +585,10 @@ __device__ __forceinline__ void gat_bwd_src_row(const EngineArgs& A, const GatBw
                                                 int64_t r, int64_t b, int64_t e, int slot) {
     const GeomDev& geo = A.geo;
     const int L = WAVE / Gn;
-    const int red = geo.F / VEC;  // lanes of a head
+    const int red = geo.FV;  // lanes of a head
     const bool active = ln.lig < geo.NV;
-    const int col0 = active ? ln.lig * VEC : 0;
-    const int h = col0 / geo.F;
+    const Cols cc = cols_of<VEC, S::OV>(geo, active, ln.lig);
+    const int col0 = cc.col0, h = cc.h;
     const bool head_lane = active && (col0 % geo.F) == 0;
     const int64_t self = r >= 0 ? r : 0;
     float x[VEC];
@@ -608,6 +618,7 @@ __device__ __forceinline__ void gat_bwd_src_row(const EngineArgs& A, const GatBw
             dp = fma(z, xd[i], dp);
             df[i] = fma(a, z, df[i]);
         }
+        if constexpr (S::OV) dp = last_share(rw.a, xd, cc.skip);
         dl = fma(al, dp, dl);
         ds = fma(al, (double)rw.rec.w, ds);
     };
@@ -623,7 +634,7 @@ __device__ __forceinline__ void gat_bwd_src_row(const EngineArgs& A, const GatBw
         dl = d_el();
         if (ln.g != 0) return;
         if (slot >= 0) {
-            const int64_t D = (int64_t)geo.NV * VEC;
+            const int64_t D = (int64_t)geo.D;
             double* p = B.part + (int64_t)slot * (D + B.H);
             if (active) {
 #pragma unroll
@@ -675,19 +686,19 @@ __global__ __launch_bounds__(256) void gat_bwd_src_kernel(EngineArgs A, GatBwdAr
         // sources without out-edges: zero gradients
         const int64_t k0 = A.sch.n_nz + ((int64_t)(w - A.sch.w_small_end) * Gn + ln.g) * A.sch.fill_rows_per_group;
         const bool active = ln.lig < geo.NV;
-        const int col0 = active ? ln.lig * VEC : 0;
+        const Cols cc = cols_of<VEC, S::OV>(geo, active, ln.lig);
         const double zero[VEC] = {};
         for (int q = 0; q < A.sch.fill_rows_per_group; ++q) {
             const int64_t k = k0 + q;
             if (k < A.sch.n_rows)
-                gat_write_src<T, VEC>(B, A.csr.perm[k], col0, col0 / geo.F, active, active && col0 % geo.F == 0,
+                gat_write_src<T, VEC>(B, A.csr.perm[k], cc.col0, cc.h, active, active && cc.col0 % geo.F == 0,
                                       zero, 0.0);
         }
     }
 }
 
 // pass B, hub rows: partials of the row's segments summed in order
-template <typename T, int VEC>
+template <typename T, int VEC, bool OV>
 __global__ __launch_bounds__(256) void gat_bwd_src_combine_kernel(EngineArgs A, GatBwdArgs B) {
     const int w = wave_id();
     const GeomDev& geo = A.geo;
@@ -697,10 +708,10 @@ __global__ __launch_bounds__(256) void gat_bwd_src_combine_kernel(EngineArgs A, 
     if (k >= A.sch.n_hub) return;
     const int64_t r = A.csr.perm[k];
     const int s0 = A.csr.hub_off[k], s1 = A.csr.hub_off[k + 1];
-    const int64_t D = (int64_t)geo.NV * VEC;
+    const int64_t D = (int64_t)geo.D;
     const bool active = ln.lig < geo.NV;
-    const int col0 = active ? ln.lig * VEC : 0;
-    const int h = col0 / geo.F;
+    const Cols cc = cols_of<VEC, OV>(geo, active, ln.lig);
+    const int col0 = cc.col0, h = cc.h;
     const bool head_lane = active && (col0 % geo.F) == 0;
     double df[VEC], dl = 0.0;
 #pragma unroll
@@ -727,55 +738,70 @@ __global__ __launch_bounds__(256) void gat_bwd_src_combine_kernel(EngineArgs A, 
 
 namespace {
 
-template <typename T, int V, bool ATTN>
+// the walks of the forward and of the backward's destination pass (feat and
+// the head's el at the neighbour), and of its source pass (dZ at the neighbour)
+template <int C, bool OV>
+using SpGat = Spec<T_NBR, OK_FULL, T_NBR, OK_HEAD, C, false, true, OV>;
+template <int C, bool OV>
+using SpGatOut = Spec<T_NBR, OK_FULL, DYN, DYN, C, false, true, OV>;
+
+template <typename T, int V>
+constexpr bool gat_fast = (sizeof(T) == 4 && V == 4) || (sizeof(T) == 2 && (V == 4 || V == 8));
+
+template <typename T, int V, bool ATTN, bool OV>
 void gat_launch_t(const EngineArgs& a, const GatArgs& g, int gc, hipStream_t s) {
     const dim3 grid(blocks_for_waves(a.sch.w_total)), block(WAVE * WPB);
-    if constexpr ((sizeof(T) == 4 && V == 4) || (sizeof(T) == 2 && (V == 4 || V == 8))) {
+    if constexpr (gat_fast<T, V>) {
         if (gc > 0) {
             GNNK_GC_DISPATCH(gc, {
-                hipLaunchKernelGGL((gat_kernel<T, V, Spec<T_NBR, OK_FULL, T_NBR, OK_HEAD, C, false>, ATTN>), grid,
-                                   block, 0, s, a, g);
+                hipLaunchKernelGGL((gat_kernel<T, V, SpGat<C, OV>, ATTN>), grid, block, 0, s, a, g);
             })
             return;
         }
     }
-    hipLaunchKernelGGL((gat_kernel<T, V, Spec<T_NBR, OK_FULL, T_NBR, OK_HEAD, 0, false>, ATTN>), grid, block, 0, s,
-                       a, g);
+    hipLaunchKernelGGL((gat_kernel<T, V, SpGat<0, OV>, ATTN>), grid, block, 0, s, a, g);
 }
 
-template <typename T, int V>
-void gat_all(const EngineArgs& a, const GatArgs& g, int gc, hipStream_t s) {
-    if (g.attn) gat_launch_t<T, V, true>(a, g, gc, s);
-    else gat_launch_t<T, V, false>(a, g, gc, s);
+template <typename T, int V, bool OV>
+void gat_ov(const EngineArgs& a, const GatArgs& g, int gc, hipStream_t s) {
+    if (g.attn) gat_launch_t<T, V, true, OV>(a, g, gc, s);
+    else gat_launch_t<T, V, false, OV>(a, g, gc, s);
     if (a.sch.n_hub > 0) {
         const dim3 block(WAVE * WPB);
         const dim3 cgrid(blocks_for_waves((a.sch.n_hub + a.geo.G - 1) / a.geo.G));
-        hipLaunchKernelGGL((gat_combine_kernel<T, V>), cgrid, block, 0, s, a, g);
+        hipLaunchKernelGGL((gat_combine_kernel<T, V, OV>), cgrid, block, 0, s, a, g);
         if (g.attn)
-            hipLaunchKernelGGL((gat_attn_segments_kernel<T, V>), dim3(blocks_for_waves(a.sch.n_seg)), block, 0, s,
+            hipLaunchKernelGGL((gat_attn_segments_kernel<T, V, OV>), dim3(blocks_for_waves(a.sch.n_seg)), block, 0, s,
                                a, g);
     }
 }
 
 template <typename T, int V>
-void gat_bwd_all(const EngineArgs& ain, const EngineArgs& aout, const GatBwdArgs& B, int gc, hipStream_t s) {
+void gat_all(const EngineArgs& a, const GatArgs& g, int gc, hipStream_t s) {
+    if constexpr ((sizeof(T) == 4 && V == 4) || (sizeof(T) == 2 && V == 8)) {
+        if (a.geo.ov) {
+            gat_ov<T, V, true>(a, g, gc, s);
+            return;
+        }
+    }
+    gat_ov<T, V, false>(a, g, gc, s);
+}
+
+template <typename T, int V, bool OV>
+void gat_bwd_ov(const EngineArgs& ain, const EngineArgs& aout, const GatBwdArgs& B, int gc, hipStream_t s) {
     const dim3 block(WAVE * WPB);
-    constexpr bool FV = (sizeof(T) == 4 && V == 4) || (sizeof(T) == 2 && (V == 4 || V == 8));
     if ((B.passes & 1) && ain.sch.w_total > 0) {
         const dim3 grid(blocks_for_waves(ain.sch.w_total));
         bool done = false;
-        if constexpr (FV) {
+        if constexpr (gat_fast<T, V>) {
             if (gc > 0) {
                 GNNK_GC_DISPATCH(gc, {
-                    hipLaunchKernelGGL((gat_bwd_dst_kernel<T, V, Spec<T_NBR, OK_FULL, T_NBR, OK_HEAD, C, false>>),
-                                       grid, block, 0, s, ain, B);
+                    hipLaunchKernelGGL((gat_bwd_dst_kernel<T, V, SpGat<C, OV>>), grid, block, 0, s, ain, B);
                 })
                 done = true;
             }
         }
-        if (!done)
-            hipLaunchKernelGGL((gat_bwd_dst_kernel<T, V, Spec<T_NBR, OK_FULL, T_NBR, OK_HEAD, 0, false>>), grid,
-                               block, 0, s, ain, B);
+        if (!done) hipLaunchKernelGGL((gat_bwd_dst_kernel<T, V, SpGat<0, OV>>), grid, block, 0, s, ain, B);
         if (ain.sch.n_hub > 0) {
             const int64_t n = (int64_t)ain.sch.n_hub * B.H;
             hipLaunchKernelGGL((gat_bwd_dst_combine_kernel<T>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s,
@@ -785,23 +811,31 @@ void gat_bwd_all(const EngineArgs& ain, const EngineArgs& aout, const GatBwdArgs
     if ((B.passes & 2) && aout.sch.w_total > 0 && (B.d_feat || B.d_el)) {
         const dim3 grid(blocks_for_waves(aout.sch.w_total));
         bool done = false;
-        if constexpr (FV) {
+        if constexpr (gat_fast<T, V>) {
             if (gc > 0) {
                 GNNK_GC_DISPATCH(gc, {
-                    hipLaunchKernelGGL((gat_bwd_src_kernel<T, V, Spec<T_NBR, OK_FULL, DYN, DYN, C, false>>), grid,
-                                       block, 0, s, aout, B);
+                    hipLaunchKernelGGL((gat_bwd_src_kernel<T, V, SpGatOut<C, OV>>), grid, block, 0, s, aout, B);
                 })
                 done = true;
             }
         }
-        if (!done)
-            hipLaunchKernelGGL((gat_bwd_src_kernel<T, V, Spec<T_NBR, OK_FULL, DYN, DYN, 0, false>>), grid, block, 0,
-                               s, aout, B);
+        if (!done) hipLaunchKernelGGL((gat_bwd_src_kernel<T, V, SpGatOut<0, OV>>), grid, block, 0, s, aout, B);
         if (aout.sch.n_hub > 0)
-            hipLaunchKernelGGL((gat_bwd_src_combine_kernel<T, V>),
+            hipLaunchKernelGGL((gat_bwd_src_combine_kernel<T, V, OV>),
                                dim3(blocks_for_waves((aout.sch.n_hub + aout.geo.G - 1) / aout.geo.G)), block, 0, s,
                                aout, B);
     }
+}
+
+template <typename T, int V>
+void gat_bwd_all(const EngineArgs& ain, const EngineArgs& aout, const GatBwdArgs& B, int gc, hipStream_t s) {
+    if constexpr ((sizeof(T) == 4 && V == 4) || (sizeof(T) == 2 && V == 8)) {
+        if (ain.geo.ov) {
+            gat_bwd_ov<T, V, true>(ain, aout, B, gc, s);
+            return;
+        }
+    }
+    gat_bwd_ov<T, V, false>(ain, aout, B, gc, s);
 }
 
 }  // namespace

@@ -5,7 +5,10 @@
 // two heads); NV = D / VEC vectors.  L = lanes per edge (power of two, at most
 // 64, L >= NV unless the row is processed in chunks of 64 vectors), and a
 // 64-lane wavefront holds G = 64 / L lane groups, each working on one edge at
-// a time.
+// a time.  Where no wide vector divides F, a head's last vector starts VEC
+// columns before the head's end and overlaps the one before it: both lanes
+// hold the same values of the shared columns and store them twice, and sums
+// over columns leave the last vector's shared ones out.
 //
 // Schedule of a row traversal (an in-CSR or the reverse graph's CSR).  Rows
 // are kept sorted by descending degree (perm).  A call splits them into:
@@ -98,6 +101,10 @@ struct GeomDev {
     int32_t log2L;
     int32_t G;       // lane groups per wavefront
     int32_t nchunk;  // chunks of 64 vectors (NV > 64)
+    int32_t FV;      // vectors per head (NV = heads * FV)
+    int32_t ov;      // columns of a head's last vector that the one before it holds too
+    int32_t D;       // columns per message row
+    uint32_t fv_magic;  // 2^31 / FV rounded up: (2 j + 1) * fv_magic / 2^32 is j / FV while NV <= 2^14
 };
 
 // flags of a row-engine call
@@ -181,6 +188,10 @@ hipError_t launch_spmm(const EngineArgs& a, int dtype, int vec, bool maxmin, int
 // SP_UE_H or SP_UE_R (gc 1, 2 or 4), and the edge gradient into a.out2
 hipError_t launch_spmm_dw(const EngineArgs& a, int dtype, int vec, int spec, int gc, hipStream_t s);
 hipError_t launch_spmm_combine(const EngineArgs& a, int dtype, int vec, bool maxmin, hipStream_t s);
+// the same for rows whose vectors overlap (spmm_ov.hip)
+hipError_t launch_spmm_ov(const EngineArgs& a, int dtype, bool maxmin, int opk, int spec, int gc, dim3 grid,
+                          dim3 block, hipStream_t s);
+hipError_t launch_spmm_combine_ov(const EngineArgs& a, int dtype, bool maxmin, dim3 grid, dim3 block, hipStream_t s);
 // edge-parallel (COO) walks, edge.hip: mode 0 = partials of split rows combined
 // in order afterwards, mode 1 = fp64 atomics into scratch (a.partial, rows x D)
 hipError_t launch_spmm_edge(const EngineArgs& a, int64_t n_pos, int64_t n_rows, int dtype, int vec, int opk, int spec,

@@ -20,7 +20,7 @@ namespace gnnk {
 template <typename T, int VEC, int OPK, int EXT, int RM, bool WAVE_ROW>
 struct SddmmSink {
     const EngineArgs& A;
-    int lig, col0, h, ch;
+    int lig, col0, h, ch, skip;
     bool active;
 
     // Runs of four lanes and batches of four edges per lane group (a per-head
@@ -34,16 +34,21 @@ struct SddmmSink {
     // and {2, 3} and then the two pairs, so the results are bit-identical.
     static constexpr bool kBatch = RM == 4 && UNR == 4;
 
+    // this lane's share of a sum over columns
+    __device__ __forceinline__ double total(const double* m) const {
+        double t = 0.0;
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) t += RM < 0 && i < skip ? 0.0 : m[i];
+        return t;
+    }
+
     __device__ __forceinline__ void batch(const Raw<VEC>* rw, const int32_t* ed) {
         double s[UNR];
 #pragma unroll
         for (int u = 0; u < UNR; ++u) {
             double m[VEC];
             combine_f64<VEC, OPK, EXT>(A, rw[u], ed[u], m);
-            double t = 0.0;
-#pragma unroll
-            for (int i = 0; i < VEC; ++i) t += m[i];
-            s[u] = t;
+            s[u] = total(m);
         }
         // Where the row's vectors come in whole runs of four (per-head dots,
         // rows of a multiple of four vectors) every run is active or inactive
@@ -94,9 +99,7 @@ struct SddmmSink {
                 else IO<T, VEC>::store(row + col0, v);
             }
         } else {
-            double s = 0.0;
-#pragma unroll
-            for (int i = 0; i < VEC; ++i) s += m[i];
+            double s = total(m);
             const int red = A.out.red;
             s = active ? s : 0.0;
             if constexpr (RM > 1) s = run_sum_c<RM>(s);
@@ -131,11 +134,11 @@ __device__ __forceinline__ void sddmm_row(const EngineArgs& A, const Lanes& ln, 
     for (int ch = 0; ch < geo.nchunk; ++ch) {
         const int j = ch * L + ln.lig;
         const bool active = j < geo.NV;
-        const int col0 = active ? j * VEC : 0;
-        const int h = col0 / geo.F;
+        const Cols cc = cols_of<VEC, S::OV>(geo, active, j);
+        const int col0 = cc.col0, h = cc.h;
         Pre<VEC> pre;
         if (r >= 0) load_pre<T, VEC, OPK, S>(A, self, col0, h, pre);
-        SddmmSink<T, VEC, OPK, EXT, RM, WAVE_ROW> sink{A, ln.lig, col0, h, ch, active};
+        SddmmSink<T, VEC, OPK, EXT, RM, WAVE_ROW> sink{A, ln.lig, col0, h, ch, cc.skip, active};
         if constexpr (WAVE_ROW) walk_row<T, VEC, OPK, EXT, S>(A, self, b, e, ln.g, G, col0, h, pre, sink);
         else walk_lane<T, VEC, OPK, EXT, S>(A, self, b, e, col0, h, pre, sink);
     }
@@ -221,6 +224,14 @@ void launch_sddmm_t(const EngineArgs& a, int opk, int ext, int spec, int gc, dim
         if (spec == SP_UV || spec == SP_VU) {
             const int red = a.out.reduce ? a.out.red : 0;
             GNNK_GC_DISPATCH(gc, launch_sddmm_fast<T, V, C>(a, opk, spec, red, grid, block, s))
+            return;
+        }
+    }
+    if constexpr ((sizeof(T) == 4 && V == 4) || (sizeof(T) == 2 && V == 8)) {
+        if (a.geo.ov) {
+            GNNK_OPK_DISPATCH(opk, GNNK_EXT3_DISPATCH(ext, {
+                hipLaunchKernelGGL((sddmm_kernel<T, V, K, X, -1, SpecDynT<true>>), grid, block, 0, s, a);
+            }))
             return;
         }
     }
