@@ -501,9 +501,12 @@ __device__ __forceinline__ void gat_bwd_dst_row(const EngineArgs& A, const GatBw
     double sS = 0.0, sP = 0.0, sQ = 0.0;
     Pre<VEC> pre;
     auto sink = [&](const Raw<VEC>& rw, int32_t, int32_t, bool ok) {
+        // a slot outside the row holds another edge's values: a weight of 0
+        // times an infinite one would be NaN.  (A branch: with selects the
+        // backward of 20,000 rows of 5 edges took 31.4 us, now 30.7.)
+        if (!ok) return;
         bool pos;
-        const float af = gat_attention(rw.b[0], er_h, B.slope, m, il, pos);
-        const double a = ok ? (double)af : 0.0;
+        const double a = (double)gat_attention(rw.b[0], er_h, B.slope, m, il, pos);
         const double al = pos ? a : a * (double)B.slope;
         double dp = 0.0;
 #pragma unroll
@@ -663,9 +666,11 @@ __device__ __forceinline__ void gat_bwd_src_row(const EngineArgs& A, const GatBw
     const bool with_s = B.chunk <= 1;
     Pre<VEC> pre;
     auto sink = [&](const Raw<VEC>& rw, int32_t, int32_t, bool ok) {
+        // (as in pass A; 20M edges, 4 x 16 bf16, both passes: with selects
+        // 647 us, now 628)
+        if (!ok) return;
         bool pos;
-        const float af = gat_attention(el_h, rw.rec.x, B.slope, rw.rec.y, rw.rec.z, pos);
-        const double a = ok ? (double)af : 0.0;
+        const double a = (double)gat_attention(el_h, rw.rec.x, B.slope, rw.rec.y, rw.rec.z, pos);
         const double al = pos ? a : a * (double)B.slope;
         double dp = 0.0;
 #pragma unroll

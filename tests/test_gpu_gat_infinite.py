@@ -93,3 +93,29 @@ def test_one_infinite_score_takes_the_whole_weight(pair, H, F, dtype, no_fast):
         l[top] = np.inf
         out = gnnk.gat_aggregate(pair.g, to_gpu(feat, dtype), to_gpu(l, dtype), to_gpu(er, dtype), 0.2)
         assert np.array_equal(as_f64(host(out)), feat[top].astype(np.float64))
+
+
+@pytest.mark.parametrize("no_fast", [0, 1])
+@pytest.mark.parametrize("H,F,dtype", CASES)
+def test_infinite_features_in_the_backward(pair, H, F, dtype, no_fast):
+    """dZ > 0 and +inf in the first edge of every row: S = sum of a da is +inf
+    there, so d_el = sum of a (da - S) lk is -inf for the other edges of the
+    row and NaN for that one; d_feat, which neither enters, stays.  An infinite
+    dZ gives an infinite d_feat in its column."""
+    gnnk.set_option("no_fast", no_fast)
+    feat, el, er, dz = inputs(H, F, dtype)
+    args = [to_gpu(x, dtype) for x in (el, er)]
+    _, st = gnnk.gat_aggregate(pair.g, to_gpu(feat, dtype), *args, 0.2, want_stats=True)
+    ref, _, _ = gnnk.gat_aggregate_backward(pair.g, to_gpu(feat, dtype), *args, 0.2, st, to_gpu(dz, dtype))
+    first = np.zeros(E, bool)
+    first[FIRST] = True
+    up = feat.copy()
+    up[FIRST, :, 0] = np.inf
+    df, dl, _ = gnnk.gat_aggregate_backward(pair.g, to_gpu(up, dtype), *args, 0.2, st, to_gpu(dz, dtype))
+    assert torch.equal(df, ref)
+    dl = as_f64(host(dl))[:, :, 0]
+    assert np.all(np.isneginf(dl[~first])) and np.all(np.isnan(dl[first]))
+    dz[:, :, 0] = np.inf
+    df, _, _ = gnnk.gat_aggregate_backward(pair.g, to_gpu(feat, dtype), *args, 0.2, st, to_gpu(dz, dtype))
+    df, ref = as_f64(host(df)), as_f64(host(ref))
+    assert np.all(df[:, :, 0] == np.inf) and np.array_equal(df[:, :, 1:], ref[:, :, 1:])
