@@ -108,12 +108,17 @@ typedef struct {
     int64_t seg_edges;      /* edges per segment of a hub row of the in-CSR */
     int64_t hub_dst_rows, hub_src_rows;   /* rows longer than their CSR's segment size */
     int64_t segments_in, segments_out;    /* segments of those rows */
-    size_t workspace_bytes;
+    size_t workspace_bytes; /* bytes of workspace that a build of this graph needs, the way it was built */
     int64_t seg_edges_out;  /* edges per segment of a hub row of the reverse graph's CSR */
     int64_t seg_edges_gather; /* the same for the reverse passes that gather node rows */
     int64_t segments_gather;  /* the segments of that finer table */
     int64_t seg_edges_in_gather; /* the in-CSR's finer segments, for the passes that gather node rows */
     int64_t segments_in_gather;  /* the segments of that table */
+    size_t kept_bytes;      /* bytes at the start of the workspace that the handle keeps using; the rest is free
+                             * once the build's work on its stream is done */
+    size_t lists_bytes;     /* bytes of the rows listed by neighbour (0: none kept) */
+    int32_t neighbour_lists; /* 1: the in-CSR's rows are listed by neighbour too, 2: the reverse graph's, 3: both */
+    int32_t reserved;
 } gnnk_graph_info;
 
 /* ------------------------------------------------------------------------ */
@@ -123,7 +128,7 @@ typedef struct {
  * the reverse graph (rows = sources, with the original edge ids), in- and
  * out-degrees, rows sorted by degree for scheduling, and the segment tables
  * of rows longer than seg_edges.  Derived arrays live in a caller-allocated
- * device workspace of graph_workspace_bytes() bytes, which the caller keeps
+ * device workspace, which the caller keeps
  * alive (with any borrowed index arrays) until graph_destroy.  Building runs
  * on the device, on `stream`: stable radix sorts of (row, edge id) pairs, so
  * each row lists its edges in ascending edge id, row offsets by binary search
@@ -136,15 +141,51 @@ typedef struct {
  * table.  The order never changes a result: segment partials are combined in
  * table order (graphs of fewer than 2^20 edges keep table order).  A graph
  * of at least 2^20 edges whose edge ids are scattered over its rows, a
- * quarter of its edges in long rows, also keeps each row listed by neighbour
- * id (16 bytes per edge of the workspace), and the passes that gather node
- * rows reduce in that order, which is as fixed as the edge-id order.
+ * quarter of its edges in long rows, can also keep each row listed by
+ * neighbour id, and the passes that gather node rows then reduce in that
+ * order, which is as fixed as the edge-id order.
  * The call synchronises `stream` once, to read back the input check and what
- * the schedules need of the sorted degrees, and graph_create_csr once more
- * before it, to refuse row offsets that cannot be walked; it allocates no
- * device memory (its temporaries are part of the workspace). */
+ * the schedules need of the sorted degrees, and graph_create_csr and
+ * graph_build_csr once more before it, to refuse row offsets that cannot be
+ * walked; it allocates no device memory. */
 
-/* Upper bound of the workspace for a graph of this size; ptr_t is the width
+/* Device memory of a build, all of it the caller's and 256-byte aligned:
+ *  - the workspace (about 28 bytes per edge), kept until graph_destroy;
+ *  - temporaries (20 bytes per edge), the caller's again as soon as the work
+ *    queued on the build's stream is done (releasing them to an allocator
+ *    ordered on that stream is enough);
+ *  - rows listed by neighbour (8 bytes per edge and direction), kept until
+ *    graph_destroy.  Their size is known only once the edges are sorted, so
+ *    `lists` is called for them, at most once during the call, on the calling
+ *    thread, and only for a graph that gains from a listing.  Listing the
+ *    edges takes about as long as the rest of the build and pays after some
+ *    ten passes over the graph; `lists` may be NULL, or return NULL: the
+ *    graph then keeps none. */
+typedef struct {
+    void* workspace;
+    size_t workspace_bytes;
+    void* temp;
+    size_t temp_bytes;
+    void* (*lists)(void* ctx, size_t bytes);
+    void* ctx;
+} gnnk_build_memory;
+
+/* Upper bounds of the workspace and the temporaries for a graph of this size
+ * (the limits of graph_workspace_bytes apply). */
+gnnk_status graph_build_bytes(int64_t num_src, int64_t num_dst, int64_t num_edges, gnnk_itype ptr_t,
+                              size_t* workspace, size_t* temp);
+
+/* graph_create_coo and graph_create_csr (below) with their memory in parts. */
+gnnk_status graph_build_coo(int64_t num_src, int64_t num_dst, int64_t num_edges, const int32_t* src,
+                            const int32_t* dst, gnnk_itype ptr_t, const gnnk_build_memory* mem, hipStream_t stream,
+                            gnnk_graph_t* out);
+gnnk_status graph_build_csr(int64_t num_src, int64_t num_dst, int64_t num_edges, const void* indptr,
+                            gnnk_itype ptr_t, const int32_t* indices, const int32_t* eids,
+                            const gnnk_build_memory* mem, hipStream_t stream, gnnk_graph_t* out);
+
+/* Upper bound of the one buffer that graph_create_coo and graph_create_csr
+ * take, workspace and temporaries together (such a graph keeps no listing by
+ * neighbour, and of its buffer only the first graph_info.kept_bytes); ptr_t is the width
  * of the CSR row offsets the handle builds (either width for any size).
  * Node counts must be below 2^31 - 1 and num_edges at most 2^31 - 2^16 - 1
  * (edge ids and CSR positions are int32, and the walks step positions past a

@@ -147,20 +147,32 @@ constexpr int32_t FLAG_PTR = 2;       // row offsets not a valid CSR
 constexpr int32_t FLAG_PERM = 4;      // edge ids not a permutation
 constexpr int32_t FLAG_NOT_IDENT = 8; // edge ids differ from in-CSR positions
 
-// Fixed-size regions first, then the hub tables whose sizes are known only
-// once the degrees are sorted.
+// What a handle keeps in the caller's workspace: fixed-size regions first,
+// then the hub tables whose sizes are known only once the degrees are sorted.
 struct Layout {
     size_t in_ptr = 0, in_idx = 0, in_eid = 0, out_ptr = 0, out_idx = 0, out_eid = 0;
     size_t in_deg = 0, out_deg = 0, in_perm = 0, out_perm = 0, in_row = 0, out_row = 0, out_pos = 0, flag = 0;
-    // E words each: temporaries of the sorts; the first four keep the rows
-    // listed by neighbour of a graph that has them
-    size_t edge_tmp[5] = {};
-    size_t tmp = 0, tmp_words = 0;  // the build's temporaries (radix-sort counts, degree sort keys)
     size_t in_hub = 0, out_hub = 0, in_seg = 0, out_seg = 0, in_sego = 0, out_sego = 0, total = 0;
     size_t fine_hub = 0, fine_seg = 0, fine_sego = 0;  // the reverse CSR's finer hub tables
     size_t in_rowt = 0, out_rowt = 0, in_segw = 0, out_segw = 0, fine_segw = 0;  // per-wavefront lookup tables
     size_t ifine_hub = 0, ifine_seg = 0, ifine_sego = 0, ifine_segw = 0;  // the in-CSR's finer hub tables
-    size_t nbr_sego[4] = {}, nbr_segw[4] = {};  // segment orders of the rows listed by neighbour
+};
+
+// Temporaries of a build, in a buffer that is the caller's again afterwards:
+// within the workspace they were 20 bytes per edge on top of the 28 that a
+// handle keeps, for as long as it lived.
+struct TempLayout {
+    size_t edge[5] = {};  // E words each: temporaries of the sorts
+    size_t words = 0;     // radix-sort counts, degree sort keys
+    size_t total = 0;
+};
+
+// Rows listed by neighbour id, in a buffer of their own that only graphs that
+// keep such a listing ask for.
+struct ListLayout {
+    size_t idx[2] = {}, eid[2] = {};   // the in-CSR's and the reverse CSR's
+    size_t sego[4] = {}, segw[4] = {};  // segment orders of the four hub tables
+    size_t total = 0;
 };
 
 struct Bump {
@@ -190,7 +202,7 @@ size_t build_tmp_words(int64_t n_src, int64_t n_dst, int64_t E) {
 
 Layout make_layout(int64_t n_src, int64_t n_dst, int64_t E, size_t ps, int64_t hub_in, int64_t hub_out, int64_t seg_in,
                    int64_t seg_out, int64_t hub_fine = 0, int64_t seg_fine = 0,
-                   int64_t hub_ifine = 0, int64_t seg_ifine = 0, bool nbr_in = false, bool nbr_out = false) {
+                   int64_t hub_ifine = 0, int64_t seg_ifine = 0) {
     Layout L;
     Bump b;
     L.in_ptr = b.take((size_t)(n_dst + 1) * ps);
@@ -206,12 +218,9 @@ Layout make_layout(int64_t n_src, int64_t n_dst, int64_t E, size_t ps, int64_t h
     L.in_row = b.take((size_t)E * 4);
     L.out_row = b.take((size_t)E * 4);
     L.out_pos = b.take((size_t)E * 4);
-    for (size_t& o : L.edge_tmp) o = b.take((size_t)E * 4);
     L.flag = b.take(sizeof(BuildSummary));
     L.in_rowt = b.take((size_t)n_dst * 16);
     L.out_rowt = b.take((size_t)n_src * 16);
-    L.tmp_words = build_tmp_words(n_src, n_dst, E);
-    L.tmp = b.take(L.tmp_words * 4);
     L.in_hub = b.take((size_t)(hub_in + 1) * 4);
     L.out_hub = b.take((size_t)(hub_out + 1) * 4);
     L.in_seg = b.take((size_t)seg_in * 16);
@@ -228,14 +237,33 @@ Layout make_layout(int64_t n_src, int64_t n_dst, int64_t E, size_t ps, int64_t h
     L.ifine_seg = b.take((size_t)seg_ifine * 16);
     L.ifine_sego = b.take((size_t)seg_ifine * 4);
     L.ifine_segw = b.take((size_t)seg_ifine * 16);
-    const int64_t segs[4] = {seg_in, seg_ifine, seg_out, seg_fine};
-    for (int t = 0; t < 4; ++t) {
-        const int64_t n = (t < 2 ? nbr_in : nbr_out) ? segs[t] : 0;
-        L.nbr_sego[t] = b.take((size_t)n * 4);
-        L.nbr_segw[t] = b.take((size_t)n * 16);
-    }
     L.total = b.off;
     return L;
+}
+
+TempLayout make_temp(int64_t n_src, int64_t n_dst, int64_t E) {
+    TempLayout T;
+    Bump b;
+    for (size_t& o : T.edge) o = b.take((size_t)E * 4);
+    T.words = b.take(build_tmp_words(n_src, n_dst, E) * 4);
+    T.total = b.off;
+    return T;
+}
+
+ListLayout make_lists(int64_t E, bool in, bool out, const int64_t* segs) {
+    ListLayout N;
+    Bump b;
+    for (int d = 0; d < 2; ++d) {
+        const bool has = d ? out : in;
+        N.idx[d] = b.take(has ? (size_t)E * 4 : 0);
+        N.eid[d] = b.take(has ? (size_t)E * 4 : 0);
+        for (int t = 2 * d; t < 2 * d + 2; ++t) {
+            N.sego[t] = b.take(has ? (size_t)segs[t] * 4 : 0);
+            N.segw[t] = b.take(has ? (size_t)segs[t] * 16 : 0);
+        }
+    }
+    N.total = b.off;
+    return N;
 }
 
 // Edge ids and CSR positions are int32.  The walks advance a position past a
@@ -261,10 +289,15 @@ int row_bits(int64_t n_rows) { return key_bits(n_rows > 1 ? (uint64_t)(n_rows - 
 
 struct Builder {
     gnnk_graph* g;
-    char* W;
-    Layout L;
-    uint32_t* scratch = nullptr;
+    gnnk_build_memory mem;
     hipStream_t s;
+    char* W = nullptr;          // the workspace
+    char* T = nullptr;          // the temporaries
+    char* N = nullptr;          // the rows listed by neighbour
+    Layout L;
+    TempLayout TL;
+    ListLayout NL;
+    uint32_t* scratch = nullptr;
     hipError_t err = hipSuccess;
 
     void chk(hipError_t x) {
@@ -281,9 +314,11 @@ struct Builder {
         return h;
     }
 
-    // the build's temporaries, regions of the workspace
-    void get_scratch() { scratch = at<uint32_t>(L.tmp); }
-    uint32_t* edge_tmp(int k) { return at<uint32_t>(L.edge_tmp[k]); }
+    uint32_t* edge_tmp(int k) { return reinterpret_cast<uint32_t*>(T + TL.edge[k]); }
+    template <typename X>
+    X* list(size_t off) {
+        return reinterpret_cast<X*>(N + off);
+    }
 
     // edges sorted stably by `row_of_e`: {row, edge id, other endpoint} per position
     static RadixSort edge_sort(const int32_t* row_of_e, const int32_t* other_of_e, int64_t E, int bits,
@@ -312,7 +347,7 @@ struct Builder {
     // The common tail: row offsets, degrees and rows by descending degree
     // (ties by row id) of both CSRs, the read-back, and the tables.  coo:
     // the in-CSR's offsets are not built yet and its edge ids not checked.
-    gnnk_status finish(size_t ws_bytes, bool coo) {
+    gnnk_status finish(bool coo) {
         const int64_t E = g->n_edges;
         Dir& in = g->in;
         Dir& out = g->out;
@@ -390,13 +425,18 @@ struct Builder {
         auto worth = [&](const Dir& f, int64_t S) {
             return in.eid && !local_ids && E >= ORDER_EDGES && 4 * f.n_seg * S >= E;
         };
-        const bool nbr_in = worth(ifine, g->seg_edges_in_fine), nbr_out = worth(fine, g->seg_edges_fine);
-        L = make_layout(g->n_src, g->n_dst, E, g->ptr64 ? 8 : 4, in.n_hub, out.n_hub, in.n_seg, out.n_seg,
-                        finer ? fine.n_hub : 0, finer ? fine.n_seg : 0, ifiner ? ifine.n_hub : 0,
-                        ifiner ? ifine.n_seg : 0, nbr_in, nbr_out);
-        if (ws_bytes < L.total)
-            return fail(GNNK_ENOMEM, "workspace of %zu bytes is smaller than the %zu bytes this graph needs",
-                        ws_bytes, L.total);
+        bool nbr_in = worth(ifine, g->seg_edges_in_fine), nbr_out = worth(fine, g->seg_edges_fine);
+        const int64_t segs[4] = {in.n_seg, ifiner ? ifine.n_seg : 0, out.n_seg, finer ? fine.n_seg : 0};
+        L = make_layout(g->n_src, g->n_dst, E, g->ptr64 ? 8 : 4, in.n_hub, out.n_hub, segs[0], segs[2],
+                        finer ? fine.n_hub : 0, segs[3], ifiner ? ifine.n_hub : 0, segs[1]);
+        if (mem.workspace_bytes < L.total) return short_of_memory(L.total);
+        if (nbr_in || nbr_out) {
+            // optional memory: a caller without it gets a graph without listings
+            NL = make_lists(E, nbr_in, nbr_out, segs);
+            N = mem.lists ? reinterpret_cast<char*>(mem.lists(mem.ctx, NL.total)) : nullptr;
+            if ((uintptr_t)N % ALIGN) return fail(GNNK_EINVAL, "memory for neighbour lists must be 256-byte aligned");
+            if (!N) nbr_in = nbr_out = false;
+        }
         in.rowt = ifine.rowt = at<int4>(L.in_rowt);
         out.rowt = fine.rowt = at<int4>(L.out_rowt);
         chk(launch_row_table(in.ptr, in.perm, in.n_rows, in.rowt, out.ptr, out.perm, out.n_rows, out.rowt, g->ptr64,
@@ -420,8 +460,8 @@ struct Builder {
             by.idx = idx;
             by.eid = eid;
             if (nbr) {
-                by.seg_order = at<int32_t>(L.nbr_sego[t]);
-                by.segw = at<int4>(L.nbr_segw[t]);
+                by.seg_order = list<int32_t>(NL.sego[t]);
+                by.segw = list<int4>(NL.segw[t]);
                 n_keep += n_own;
             }
             H.table[t] = {by.rowt, by.idx, by.hub_off, by.seg, by.seg_order, by.segw, own ? by.n_hub : 0, S, n_seg};
@@ -448,11 +488,18 @@ struct Builder {
         build_segments(H, n_seg);
         chk(launch_seg_wave(K, n_keep, nullptr, s));
         // the position of each edge id in the reverse CSR that the max/min
-        // backward walks (last: its array is a temporary until here)
+        // backward walks (last: its array is a temporary of the edge sort)
         chk(launch_edge_ids(g->out_nbr.eid, out.pos, nullptr, E, g->flag, FLAG_NOT_IDENT, s));
         if (err != hipSuccess) return hip_fail(err, "graph build");
         g->ws_used = L.total;
+        g->listed = (nbr_in ? 1 : 0) + (nbr_out ? 2 : 0);
+        g->lists_bytes = g->listed ? NL.total : 0;
         return GNNK_OK;
+    }
+
+    gnnk_status short_of_memory(size_t need) {
+        return fail(GNNK_ENOMEM, "workspace of %zu bytes is smaller than the %zu bytes this graph needs",
+                    mem.workspace_bytes, need);
     }
 
     // A second listing of each row of a CSR, by neighbour id (ties by edge
@@ -471,35 +518,16 @@ struct Builder {
     // the gathers gain, and where few edges lie in hub rows there is nothing
     // to gain: those graphs are left as they are.
     void list_by_neighbour(bool nbr_in, bool nbr_out) {
-        const int64_t E = g->n_edges;
-        Dir& in = g->in;
-        Dir& out = g->out;
         auto u = [](const int32_t* p) { return const_cast<uint32_t*>(reinterpret_cast<const uint32_t*>(p)); };
-        uint32_t* pos = u(out.pos);
-        if (nbr_in) {
-            const RadixSort r{{u(out.idx), u(out.eid), u(out.row)}, {pos, edge_tmp(0), edge_tmp(1)},
-                              {edge_tmp(4), edge_tmp(2), edge_tmp(3)}, E, row_bits(g->n_dst)};
+        auto list_by = [&](int d, const Dir& other, int64_t n_rows, Dir& by) {
+            by.idx = list<int32_t>(NL.idx[d]);
+            by.eid = list<int32_t>(NL.eid[d]);
+            const RadixSort r{{u(other.idx), u(other.eid), u(other.row)}, {edge_tmp(0), u(by.eid), u(by.idx)},
+                              {edge_tmp(1), edge_tmp(2), edge_tmp(3)}, g->n_edges, row_bits(n_rows)};
             chk(radix_sort(&r, 1, scratch, s));
-            g->in_nbr.eid = at<int32_t>(L.edge_tmp[0]);
-            g->in_nbr.idx = at<int32_t>(L.edge_tmp[1]);
-        }
-        if (nbr_out) {
-            // the arrays that are free are too few: the rows of the reverse
-            // CSR's positions, and those of the in-CSR's once the first pass
-            // has read them, serve as temporaries and are written anew
-            const int bits = row_bits(g->n_src);
-            RadixSort r{{u(in.idx), u(in.eid), u(in.row)}, {u(in.row), edge_tmp(2), edge_tmp(3)},
-                        {edge_tmp(4), pos, u(out.row)}, E, bits};
-            if (radix_passes(bits) % 2) {
-                r.out.key = edge_tmp(4);
-                r.tmp = {pos, u(out.row), u(in.row)};
-            }
-            chk(radix_sort(&r, 1, scratch, s));
-            g->out_nbr.eid = at<int32_t>(L.edge_tmp[2]);
-            g->out_nbr.idx = at<int32_t>(L.edge_tmp[3]);
-            chk(launch_fill_rows(in.ptr, g->ptr64, g->n_dst, E, in.row, s));
-            chk(launch_fill_rows(out.ptr, g->ptr64, g->n_src, E, out.row, s));
-        }
+        };
+        if (nbr_in) list_by(0, g->out, g->n_dst, g->in_nbr);
+        if (nbr_out) list_by(1, g->in, g->n_src, g->out_nbr);
     }
 
     // The segments of hub rows and the order in which wavefronts take them:
@@ -514,20 +542,18 @@ struct Builder {
         const bool ordered = n_seg > 0 && g->n_edges >= ORDER_EDGES;
         // 32-bit keys: ids of more than 30 bits lose their lowest ones
         const int bits = row_bits(std::max(g->n_src, g->n_dst)), id_bits = std::min(bits, 30);
-        // five arrays of n_seg words, at most E / 4: the last edge-sized
-        // temporary in quarters, and the array of the edges' positions
-        uint32_t* t = edge_tmp(4);
-        uint32_t* key = ordered ? t : nullptr;
+        // (fewer segments than edges: an edge-sized temporary holds an array)
+        uint32_t* key = ordered ? edge_tmp(0) : nullptr;
         chk(launch_hub_tables(H, n_seg, id_bits, bits - id_bits, key, s));
         if (!ordered) {
             chk(launch_seg_wave(H, n_seg, nullptr, s));
             return;
         }
         // one sort of all tables, the table number above the neighbour ids
-        const RadixSort r{{key, nullptr, nullptr}, {reinterpret_cast<uint32_t*>(g->out.pos), t + n_seg, nullptr},
-                          {t + 2 * n_seg, t + 3 * n_seg, nullptr}, n_seg, id_bits + 2};
+        const RadixSort r{{key, nullptr, nullptr}, {edge_tmp(1), edge_tmp(2), nullptr},
+                          {edge_tmp(3), edge_tmp(4), nullptr}, n_seg, id_bits + 2};
         chk(radix_sort(&r, 1, scratch, s));
-        chk(launch_seg_wave(H, n_seg, t + n_seg, s));
+        chk(launch_seg_wave(H, n_seg, edge_tmp(2), s));
     }
 };
 
@@ -549,27 +575,31 @@ gnnk_graph* new_graph(int64_t num_src, int64_t num_dst, int64_t num_edges, gnnk_
     return g;
 }
 
-// workspace checks shared by both constructors; fills b.W, b.L, g->flag
-gnnk_status begin_build(Builder& b, void* ws, size_t ws_bytes) {
+// memory checks shared by both constructors; fills b.W, b.T, b.L, g->flag
+gnnk_status begin_build(Builder& b) {
     gnnk_graph* g = b.g;
     b.L = make_layout(g->n_src, g->n_dst, g->n_edges, g->ptr64 ? 8 : 4, 0, 0, 0, 0);
-    if (!ws || ws_bytes < b.L.total)
-        return fail(GNNK_ENOMEM, "workspace of %zu bytes is smaller than the %zu bytes this graph needs", ws_bytes,
-                    b.L.total);
-    b.W = reinterpret_cast<char*>(ws);
+    b.TL = make_temp(g->n_src, g->n_dst, g->n_edges);
+    if (!b.mem.workspace || b.mem.workspace_bytes < b.L.total) return b.short_of_memory(b.L.total);
+    if (!b.mem.temp || b.mem.temp_bytes < b.TL.total)
+        return fail(GNNK_ENOMEM, "temporaries of %zu bytes are smaller than the %zu bytes this build needs",
+                    b.mem.temp_bytes, b.TL.total);
+    b.W = reinterpret_cast<char*>(b.mem.workspace);
+    b.T = reinterpret_cast<char*>(b.mem.temp);
     if ((uintptr_t)b.W % ALIGN) return fail(GNNK_EINVAL, "workspace must be 256-byte aligned");
+    if ((uintptr_t)b.T % ALIGN) return fail(GNNK_EINVAL, "temporaries must be 256-byte aligned");
+    b.scratch = reinterpret_cast<uint32_t*>(b.T + b.TL.words);
     g->flag = b.at<int32_t>(b.L.flag);
     b.chk(hipMemsetAsync(g->flag, 0, offsetof(BuildSummary, n_hub), b.s));  // the flag word and near_ids
     return GNNK_OK;
 }
 
-gnnk_status create_coo(Builder& b, const int32_t* src, const int32_t* dst, void* ws, size_t ws_bytes) {
+gnnk_status create_coo(Builder& b, const int32_t* src, const int32_t* dst) {
     gnnk_graph* g = b.g;
     const int64_t E = g->n_edges;
-    gnnk_status st = begin_build(b, ws, ws_bytes);
+    gnnk_status st = begin_build(b);
     if (st != GNNK_OK) return st;
     b.chk(launch_validate(src, g->n_src, dst, g->n_dst, E, g->flag, b.s));
-    b.get_scratch();
     const Layout& L = b.L;
     Dir& in = g->in;
     in.ptr = b.W + L.in_ptr;
@@ -580,14 +610,13 @@ gnnk_status create_coo(Builder& b, const int32_t* src, const int32_t* dst, void*
     // source, ties in edge-id order
     const RadixSort sorts[2] = {b.in_sort(src, dst), b.out_sort(src, dst)};
     b.chk(radix_sort(sorts, 2, b.scratch, b.s));
-    return b.finish(ws_bytes, true);
+    return b.finish(true);
 }
 
-gnnk_status create_csr(Builder& b, const void* indptr, const int32_t* indices, const int32_t* eids, void* ws,
-                       size_t ws_bytes) {
+gnnk_status create_csr(Builder& b, const void* indptr, const int32_t* indices, const int32_t* eids) {
     gnnk_graph* g = b.g;
     const int64_t E = g->n_edges;
-    gnnk_status st = begin_build(b, ws, ws_bytes);
+    gnnk_status st = begin_build(b);
     if (st != GNNK_OK) return st;
     const Layout& L = b.L;
     b.chk(launch_validate_ptr(indptr, g->ptr64, g->n_dst, E, g->flag, b.s));
@@ -602,7 +631,6 @@ gnnk_status create_csr(Builder& b, const void* indptr, const int32_t* indices, c
         return fail(GNNK_EINVAL, "indptr must start at 0, end at num_edges and never decrease");
     if (h & FLAG_INDEX) return fail(GNNK_EINVAL, "an index is out of range");
     if (h & FLAG_PERM) return fail(GNNK_EINVAL, "eids is not a permutation of 0..num_edges-1");
-    b.get_scratch();
     const bool identity = !eids || !(h & FLAG_NOT_IDENT);
     g->identity_eids = identity;
     Dir& in = g->in;
@@ -620,7 +648,56 @@ gnnk_status create_csr(Builder& b, const void* indptr, const int32_t* indices, c
     }
     const RadixSort sort = b.out_sort(src_of_e, dst_of_e);
     b.chk(radix_sort(&sort, 1, b.scratch, b.s));
-    return b.finish(ws_bytes, false);
+    return b.finish(false);
+}
+
+// the most that a handle of these sizes keeps, whatever its degrees
+size_t kept_bound(int64_t num_src, int64_t num_dst, int64_t num_edges, gnnk_itype ptr_t) {
+    // hub rows have more than S edges: at most E / S of them, and at most
+    // E / S + (hub rows) <= 2 E / S segments
+    const int64_t Si = seg_edges_for(num_edges, false), So = seg_edges_for(num_edges, true);
+    const int64_t Sf = seg_edges_fine_for(num_edges);  // both CSRs' finer tables
+    return make_layout(num_src, num_dst, num_edges, ptr_t == GNNK_I64 ? 8 : 4, num_edges / Si + 1,
+                       num_edges / So + 1, max_segments(num_edges, Si), max_segments(num_edges, So),
+                       Sf < So ? num_edges / Sf + 1 : 0, Sf < So ? max_segments(num_edges, Sf) : 0,
+                       Sf < Si ? num_edges / Sf + 1 : 0, Sf < Si ? max_segments(num_edges, Sf) : 0)
+        .total;
+}
+
+gnnk_status check_sizes(int64_t num_src, int64_t num_dst, int64_t num_edges, gnnk_itype ptr_t) {
+    if (!sizes_ok(num_src, num_dst, num_edges))
+        return fail(GNNK_EINVAL, "sizes out of range (node counts < 2^31 - 1, edges <= 2^31 - 2^16 - 1)");
+    if (ptr_t != GNNK_I32 && ptr_t != GNNK_I64) return fail(GNNK_EINVAL, "bad ptr type");
+    return GNNK_OK;
+}
+
+// one buffer for everything: the temporaries at its end
+gnnk_build_memory one_buffer(int64_t num_src, int64_t num_dst, int64_t num_edges, void* workspace, size_t ws_bytes) {
+    const size_t temp = make_temp(num_src, num_dst, num_edges).total;
+    if (!workspace || ws_bytes < temp) return {workspace, ws_bytes, nullptr, 0, nullptr, nullptr};
+    const size_t at = (ws_bytes - temp) / ALIGN * ALIGN;
+    return {workspace, at, reinterpret_cast<char*>(workspace) + at, ws_bytes - at, nullptr, nullptr};
+}
+
+gnnk_status build_coo(int64_t num_src, int64_t num_dst, int64_t num_edges, const int32_t* src, const int32_t* dst,
+                      gnnk_itype ptr_t, const gnnk_build_memory& mem, hipStream_t stream, gnnk_graph_t* out) {
+    if (num_edges > 0 && (!src || !dst)) return fail(GNNK_EINVAL, "src/dst is NULL");
+    Builder b{new_graph(num_src, num_dst, num_edges, ptr_t), mem, stream};
+    const gnnk_status st = create_coo(b, src, dst);
+    if (st != GNNK_OK) free_graph(b.g);
+    else *out = b.g;
+    return st;
+}
+
+gnnk_status build_csr(int64_t num_src, int64_t num_dst, int64_t num_edges, const void* indptr, gnnk_itype ptr_t,
+                      const int32_t* indices, const int32_t* eids, const gnnk_build_memory& mem, hipStream_t stream,
+                      gnnk_graph_t* out) {
+    if (!indptr || (num_edges > 0 && !indices)) return fail(GNNK_EINVAL, "indptr/indices is NULL");
+    Builder b{new_graph(num_src, num_dst, num_edges, ptr_t), mem, stream};
+    const gnnk_status st = create_csr(b, indptr, indices, eids);
+    if (st != GNNK_OK) free_graph(b.g);
+    else *out = b.g;
+    return st;
 }
 
 }  // namespace
@@ -630,23 +707,46 @@ using namespace gnnk;
 
 extern "C" {
 
+gnnk_status graph_build_bytes(int64_t num_src, int64_t num_dst, int64_t num_edges, gnnk_itype ptr_t,
+                              size_t* workspace, size_t* temp) {
+    clear_error();
+    if (!workspace || !temp) return fail(GNNK_EINVAL, "workspace or temp is NULL");
+    const gnnk_status st = check_sizes(num_src, num_dst, num_edges, ptr_t);
+    if (st != GNNK_OK) return st;
+    *workspace = kept_bound(num_src, num_dst, num_edges, ptr_t);
+    *temp = make_temp(num_src, num_dst, num_edges).total;
+    return GNNK_OK;
+}
+
 gnnk_status graph_workspace_bytes(int64_t num_src, int64_t num_dst, int64_t num_edges, gnnk_itype ptr_t,
                                   size_t* bytes) {
     clear_error();
     if (!bytes) return fail(GNNK_EINVAL, "bytes is NULL");
-    if (!sizes_ok(num_src, num_dst, num_edges)) return fail(GNNK_EINVAL, "sizes out of range (node counts < 2^31 - 1, edges <= 2^31 - 2^16 - 1)");
-    if (ptr_t != GNNK_I32 && ptr_t != GNNK_I64) return fail(GNNK_EINVAL, "bad ptr type");
-    // hub rows have more than S edges: at most E / S of them, and at most
-    // E / S + (hub rows) <= 2 E / S segments
-    const int64_t Si = seg_edges_for(num_edges, false), So = seg_edges_for(num_edges, true);
-    const int64_t Sf = seg_edges_fine_for(num_edges);  // both CSRs' finer tables
-    Layout L = make_layout(num_src, num_dst, num_edges, ptr_t == GNNK_I64 ? 8 : 4, num_edges / Si + 1,
-                           num_edges / So + 1, max_segments(num_edges, Si),
-                           max_segments(num_edges, So), Sf < So ? num_edges / Sf + 1 : 0,
-                           Sf < So ? max_segments(num_edges, Sf) : 0, Sf < Si ? num_edges / Sf + 1 : 0,
-                           Sf < Si ? max_segments(num_edges, Sf) : 0, true, true);
-    *bytes = L.total;
+    const gnnk_status st = check_sizes(num_src, num_dst, num_edges, ptr_t);
+    if (st != GNNK_OK) return st;
+    *bytes = kept_bound(num_src, num_dst, num_edges, ptr_t) + make_temp(num_src, num_dst, num_edges).total;
     return GNNK_OK;
+}
+
+gnnk_status graph_build_coo(int64_t num_src, int64_t num_dst, int64_t num_edges, const int32_t* src,
+                            const int32_t* dst, gnnk_itype ptr_t, const gnnk_build_memory* mem, hipStream_t stream,
+                            gnnk_graph_t* out) {
+    clear_error();
+    if (!mem || !out) return fail(GNNK_EINVAL, "mem or out is NULL");
+    *out = nullptr;
+    const gnnk_status st = check_sizes(num_src, num_dst, num_edges, ptr_t);
+    return st == GNNK_OK ? build_coo(num_src, num_dst, num_edges, src, dst, ptr_t, *mem, stream, out) : st;
+}
+
+gnnk_status graph_build_csr(int64_t num_src, int64_t num_dst, int64_t num_edges, const void* indptr,
+                            gnnk_itype ptr_t, const int32_t* indices, const int32_t* eids,
+                            const gnnk_build_memory* mem, hipStream_t stream, gnnk_graph_t* out) {
+    clear_error();
+    if (!mem || !out) return fail(GNNK_EINVAL, "mem or out is NULL");
+    *out = nullptr;
+    const gnnk_status st = check_sizes(num_src, num_dst, num_edges, ptr_t);
+    return st == GNNK_OK ? build_csr(num_src, num_dst, num_edges, indptr, ptr_t, indices, eids, *mem, stream, out)
+                         : st;
 }
 
 gnnk_status graph_create_coo(int64_t num_src, int64_t num_dst, int64_t num_edges, const int32_t* src,
@@ -655,17 +755,12 @@ gnnk_status graph_create_coo(int64_t num_src, int64_t num_dst, int64_t num_edges
     clear_error();
     if (!out) return fail(GNNK_EINVAL, "out is NULL");
     *out = nullptr;
-    if (!sizes_ok(num_src, num_dst, num_edges)) return fail(GNNK_EINVAL, "sizes out of range (node counts < 2^31 - 1, edges <= 2^31 - 2^16 - 1)");
-    if (ptr_t != GNNK_I32 && ptr_t != GNNK_I64) return fail(GNNK_EINVAL, "bad ptr type");
-    if (num_edges > 0 && (!src || !dst)) return fail(GNNK_EINVAL, "src/dst is NULL");
-    Builder b{new_graph(num_src, num_dst, num_edges, ptr_t), nullptr, {}, nullptr, stream};
-    gnnk_status st = create_coo(b, src, dst, workspace, ws_bytes);
-    if (st != GNNK_OK) {
-        free_graph(b.g);
-        return st;
-    }
-    *out = b.g;
-    return GNNK_OK;
+    gnnk_status st = check_sizes(num_src, num_dst, num_edges, ptr_t);
+    if (st != GNNK_OK) return st;
+    const gnnk_build_memory mem = one_buffer(num_src, num_dst, num_edges, workspace, ws_bytes);
+    st = build_coo(num_src, num_dst, num_edges, src, dst, ptr_t, mem, stream, out);
+    if (st == GNNK_OK) (*out)->one_buffer = true;
+    return st;
 }
 
 gnnk_status graph_create_csr(int64_t num_src, int64_t num_dst, int64_t num_edges, const void* indptr,
@@ -674,17 +769,12 @@ gnnk_status graph_create_csr(int64_t num_src, int64_t num_dst, int64_t num_edges
     clear_error();
     if (!out) return fail(GNNK_EINVAL, "out is NULL");
     *out = nullptr;
-    if (!sizes_ok(num_src, num_dst, num_edges)) return fail(GNNK_EINVAL, "sizes out of range (node counts < 2^31 - 1, edges <= 2^31 - 2^16 - 1)");
-    if (ptr_t != GNNK_I32 && ptr_t != GNNK_I64) return fail(GNNK_EINVAL, "bad ptr type");
-    if (!indptr || (num_edges > 0 && !indices)) return fail(GNNK_EINVAL, "indptr/indices is NULL");
-    Builder b{new_graph(num_src, num_dst, num_edges, ptr_t), nullptr, {}, nullptr, stream};
-    gnnk_status st = create_csr(b, indptr, indices, eids, workspace, ws_bytes);
-    if (st != GNNK_OK) {
-        free_graph(b.g);
-        return st;
-    }
-    *out = b.g;
-    return GNNK_OK;
+    gnnk_status st = check_sizes(num_src, num_dst, num_edges, ptr_t);
+    if (st != GNNK_OK) return st;
+    const gnnk_build_memory mem = one_buffer(num_src, num_dst, num_edges, workspace, ws_bytes);
+    st = build_csr(num_src, num_dst, num_edges, indptr, ptr_t, indices, eids, mem, stream, out);
+    if (st == GNNK_OK) (*out)->one_buffer = true;
+    return st;
 }
 
 gnnk_status graph_info(gnnk_graph_t g, gnnk_graph_info* info) {
@@ -709,7 +799,12 @@ gnnk_status graph_info(gnnk_graph_t g, gnnk_graph_info* info) {
     info->hub_src_rows = g->out.n_hub;
     info->segments_in = g->in.n_seg;
     info->segments_out = g->out.n_seg;
-    info->workspace_bytes = g->ws_used;
+    info->workspace_bytes =
+        g->ws_used + (g->one_buffer ? make_temp(g->n_src, g->n_dst, g->n_edges).total : 0);
+    info->kept_bytes = g->ws_used;
+    info->lists_bytes = g->lists_bytes;
+    info->neighbour_lists = g->listed;
+    info->reserved = 0;
     return GNNK_OK;
 }
 

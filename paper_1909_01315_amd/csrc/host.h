@@ -59,7 +59,10 @@ struct gnnk_graph {
     // A pass over these reaches edges through eid in any order.
     gnnk::Dir in_nbr, in_fine_nbr, out_nbr, out_fine_nbr;
     int32_t* flag = nullptr;  // device word for graph_validate
-    size_t ws_used = 0;
+    size_t ws_used = 0;            // bytes of the workspace that the handle keeps
+    size_t lists_bytes = 0;        // and of the rows listed by neighbour
+    int listed = 0;                // 1: the in-CSR's, 2: the reverse graph's CSR's
+    bool one_buffer = false;       // built by graph_create_*: temporaries after the kept arrays
     // scratch buffers the caller lent to the handle, one per stream
     static constexpr int MAX_STREAMS = 16;
     struct Lent {

@@ -12,9 +12,11 @@ dimensions contiguous (the row stride may be larger).
 """
 from __future__ import annotations
 
+import contextlib
 import ctypes
 import os
 import struct
+import threading
 
 import torch
 
@@ -51,7 +53,27 @@ class _Info(ctypes.Structure):
                 ("segments_in", ctypes.c_int64), ("segments_out", ctypes.c_int64),
                 ("workspace_bytes", ctypes.c_size_t), ("seg_edges_out", ctypes.c_int64),
                 ("seg_edges_gather", ctypes.c_int64), ("segments_gather", ctypes.c_int64),
-                ("seg_edges_in_gather", ctypes.c_int64), ("segments_in_gather", ctypes.c_int64)]
+                ("seg_edges_in_gather", ctypes.c_int64), ("segments_in_gather", ctypes.c_int64),
+                ("kept_bytes", ctypes.c_size_t), ("lists_bytes", ctypes.c_size_t),
+                ("neighbour_lists", ctypes.c_int32), ("reserved", ctypes.c_int32)]
+
+
+# gnnk_build_memory (workspace, bytes, temporaries, bytes, lists, ctx) as bytes
+_MEMORY = struct.Struct("=QQQQQQ")
+# what the build that runs on this thread gives its neighbour lists: device, tensor
+_building = threading.local()
+
+
+@ctypes.CFUNCTYPE(ctypes.c_void_p, ctypes.c_void_p, ctypes.c_size_t)
+def _allocate_lists(_ctx, nbytes):
+    try:
+        _building.lists = torch.empty(nbytes, dtype=torch.uint8, device=_building.device)
+    except RuntimeError:  # out of memory: the graph does without
+        return None
+    return _building.lists.data_ptr()
+
+
+_ALLOCATE_LISTS = ctypes.cast(_allocate_lists, ctypes.c_void_p).value
 
 
 SYMBOLS = {
@@ -61,6 +83,12 @@ SYMBOLS = {
     "graph_create_csr": [ctypes.c_int64, ctypes.c_int64, ctypes.c_int64, ctypes.c_void_p, ctypes.c_int,
                          ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p, ctypes.c_size_t, ctypes.c_void_p,
                          ctypes.c_void_p],
+    "graph_build_bytes": [ctypes.c_int64, ctypes.c_int64, ctypes.c_int64, ctypes.c_int, ctypes.c_void_p,
+                          ctypes.c_void_p],
+    "graph_build_coo": [ctypes.c_int64, ctypes.c_int64, ctypes.c_int64, ctypes.c_void_p, ctypes.c_void_p,
+                        ctypes.c_int, ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p],
+    "graph_build_csr": [ctypes.c_int64, ctypes.c_int64, ctypes.c_int64, ctypes.c_void_p, ctypes.c_int,
+                        ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p],
     "graph_info": [ctypes.c_void_p, ctypes.c_void_p],
     "graph_in_degrees": [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p],
     "graph_out_degrees": [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p],
@@ -239,40 +267,54 @@ class Graph:
         _check(load().graph_attach_scratch(self.handle, s.cuda_stream, buf.data_ptr(), size))
         self._lent[s.cuda_stream] = buf
 
-    @staticmethod
-    def _workspace(num_src, num_dst, num_edges, ptr_t, device):
-        nbytes = ctypes.c_size_t(0)
-        _check(load().graph_workspace_bytes(num_src, num_dst, num_edges, ptr_t, ctypes.byref(nbytes)))
-        return torch.empty(max(nbytes.value, 1), dtype=torch.uint8, device=device)
+    @classmethod
+    def _build(cls, fn, args, borrowed, num_src, num_dst, num_edges, ptr_t, device, neighbour_lists, stream):
+        """fn (graph_build_coo or graph_build_csr) with args and the memory of
+        the build: the handle keeps the workspace and its neighbour lists, the
+        temporaries go back to torch's allocator, which reuses them only for
+        work ordered after the build on its stream."""
+        ws_bytes, tmp_bytes = ctypes.c_size_t(0), ctypes.c_size_t(0)
+        _check(load().graph_build_bytes(num_src, num_dst, num_edges, ptr_t, ctypes.byref(ws_bytes),
+                                        ctypes.byref(tmp_bytes)))
+        ws = torch.empty(ws_bytes.value, dtype=torch.uint8, device=device)
+        with torch.cuda.stream(stream) if stream is not None else contextlib.nullcontext():
+            tmp = torch.empty(tmp_bytes.value, dtype=torch.uint8, device=device)
+        _building.device, _building.lists = device, None
+        mem = _MEMORY.pack(ws.data_ptr(), ws_bytes.value, tmp.data_ptr(), tmp_bytes.value,
+                           _ALLOCATE_LISTS if neighbour_lists else 0, 0)
+        h = ctypes.c_void_p()
+        try:
+            _check(fn(num_src, num_dst, num_edges, *args, mem, _stream(stream), ctypes.byref(h)))
+            return cls(h, [ws, _building.lists, *borrowed], num_src, num_dst, num_edges)
+        finally:
+            _building.lists = None
 
     @classmethod
     def from_coo(cls, src: torch.Tensor, dst: torch.Tensor, num_src: int, num_dst: int, ptr64: bool = False,
-                 stream=None) -> "Graph":
+                 stream=None, neighbour_lists: bool = True) -> "Graph":
+        """The graph of an edge list.  neighbour_lists: whether a graph that
+        gains from it may also list its rows by neighbour (8 bytes per edge
+        and direction, and about the time of the build once more, which pays
+        after some ten passes over the graph)."""
         assert src.dtype == torch.int32 and dst.dtype == torch.int32 and src.is_cuda and dst.is_cuda
         src, dst = src.contiguous(), dst.contiguous()
-        E = src.numel()
         ptr_t = I64 if ptr64 else I32
-        ws = cls._workspace(num_src, num_dst, E, ptr_t, src.device)
-        h = ctypes.c_void_p()
-        _check(load().graph_create_coo(num_src, num_dst, E, src.data_ptr(), dst.data_ptr(), ptr_t, ws.data_ptr(),
-                                       ws.numel(), _stream(stream), ctypes.byref(h)))
-        return cls(h, [ws], num_src, num_dst, E)
+        return cls._build(load().graph_build_coo, (src.data_ptr(), dst.data_ptr(), ptr_t), (), num_src, num_dst,
+                          src.numel(), ptr_t, src.device, neighbour_lists, stream)
 
     @classmethod
-    def from_csr(cls, indptr: torch.Tensor, indices: torch.Tensor, eids, num_src: int, stream=None) -> "Graph":
+    def from_csr(cls, indptr: torch.Tensor, indices: torch.Tensor, eids, num_src: int, stream=None,
+                 neighbour_lists: bool = True) -> "Graph":
+        """The graph of an in-CSR, whose arrays it keeps (neighbour_lists: as for from_coo)."""
         assert indptr.dtype in (torch.int32, torch.int64) and indices.dtype == torch.int32
         indptr, indices = indptr.contiguous(), indices.contiguous()
         if eids is not None:
             assert eids.dtype == torch.int32
             eids = eids.contiguous()
-        num_dst = indptr.numel() - 1
-        E = indices.numel()
         ptr_t = I64 if indptr.dtype == torch.int64 else I32
-        ws = cls._workspace(num_src, num_dst, E, ptr_t, indices.device)
-        h = ctypes.c_void_p()
-        _check(load().graph_create_csr(num_src, num_dst, E, indptr.data_ptr(), ptr_t, indices.data_ptr(),
-                                       _ptr(eids), ws.data_ptr(), ws.numel(), _stream(stream), ctypes.byref(h)))
-        return cls(h, [ws, indptr, indices, eids], num_src, num_dst, E)
+        return cls._build(load().graph_build_csr, (indptr.data_ptr(), ptr_t, indices.data_ptr(), _ptr(eids)),
+                          (indptr, indices, eids), num_src, indptr.numel() - 1, indices.numel(), ptr_t,
+                          indices.device, neighbour_lists, stream)
 
     @property
     def handle(self):

@@ -77,3 +77,20 @@ def test_workspace_bound_grows_with_size(lib):
     assert lib.graph_workspace_bytes(10, 10, top, gnnk.I64, ctypes.byref(b1)) == gnnk.OK
     assert lib.graph_workspace_bytes(10, 10, top + 1, gnnk.I64, ctypes.byref(b1)) == gnnk.EINVAL
     assert lib.graph_workspace_bytes((1 << 31) - 1, 10, 10, gnnk.I32, ctypes.byref(b1)) == gnnk.EINVAL
+
+
+def test_what_a_handle_keeps(lib):
+    """28 bytes per edge and the tables of hub rows stay with the handle; the
+    build's temporaries are counted apart, and the one buffer of the other
+    constructors holds both"""
+    one, kept, temp = (ctypes.c_size_t(0) for _ in range(3))
+    E = 114_600_000
+    assert lib.graph_build_bytes(232965, 232965, E, gnnk.I32, ctypes.byref(kept), ctypes.byref(temp)) == gnnk.OK
+    assert lib.graph_workspace_bytes(232965, 232965, E, gnnk.I32, ctypes.byref(one)) == gnnk.OK
+    assert 28 * E <= kept.value <= 30 * E
+    assert kept.value + temp.value == one.value
+    assert lib.graph_build_bytes(10, 10, 10, 7, ctypes.byref(kept), ctypes.byref(temp)) == gnnk.EINVAL
+    assert lib.graph_build_bytes(10, 10, 10, gnnk.I32, None, ctypes.byref(temp)) == gnnk.EINVAL
+    h = ctypes.c_void_p()
+    assert lib.graph_build_coo(10, 10, 0, None, None, gnnk.I32, None, None, ctypes.byref(h)) == gnnk.EINVAL
+    assert lib.graph_build_csr(10, 10, 0, None, gnnk.I32, None, None, None, None, ctypes.byref(h)) == gnnk.EINVAL
