@@ -430,6 +430,13 @@ gnnk_status gat_aggregate_backward(gnnk_graph_t g, const gnnk_tensor* feat, cons
  *                 whole batches of it: 0 (default) two where a batch holds
  *                 64 or more edges (16 or more lane groups), else one;
  *                 otherwise 1-8 (results do not depend on it)
+ *   "order_edges" at graph creation: edges from which a build orders its
+ *                 segments by the neighbours they cover and may list rows by
+ *                 neighbour: 0 (default) 2^20, otherwise 1 to 2^31 - 2^16 - 1
+ *   "neighbour_lists" at graph creation, of graphs with explicit edge ids:
+ *                 -1 (default) the directions that gain from a listing by
+ *                 neighbour; otherwise 1 for the in-CSR, 2 for the reverse
+ *                 graph's CSR, 3 for both, 0 for none
  *   "small_deg"   rows of at most this many edges take one lane group each
  *                 and share a wavefront (-1 = auto: 32, or the lane groups
  *                 per wavefront if more; none when a wavefront is one group)

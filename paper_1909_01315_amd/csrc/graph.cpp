@@ -279,7 +279,7 @@ bool sizes_ok(int64_t n_src, int64_t n_dst, int64_t E) {
 // cover: below it a graph has at most 4 x 2^20 / 32 segments, few enough to be
 // in flight together, and the sort's launches would be a good part of a
 // mini-batch block's build
-constexpr int64_t ORDER_EDGES = (int64_t)1 << 20;
+int64_t order_edges() { return options().order_edges > 0 ? options().order_edges : (int64_t)1 << 20; }
 
 // the longest rows that the edge softmax still gives to one wavefront
 int64_t far_degree(const gnnk_graph* g) { return std::max<int64_t>(g->seg_edges, 2048); }
@@ -423,9 +423,13 @@ struct Builder {
         }
         const bool local_ids = 2 * sum.near_ids >= SUMMARY_SAMPLES;
         auto worth = [&](const Dir& f, int64_t S) {
-            return in.eid && !local_ids && E >= ORDER_EDGES && 4 * f.n_seg * S >= E;
+            return in.eid && !local_ids && E >= order_edges() && 4 * f.n_seg * S >= E;
         };
         bool nbr_in = worth(ifine, g->seg_edges_in_fine), nbr_out = worth(fine, g->seg_edges_fine);
+        if (const int64_t o = options().neighbour_lists; o >= 0) {
+            nbr_in = in.eid && (o & 1);
+            nbr_out = in.eid && (o & 2);
+        }
         const int64_t segs[4] = {in.n_seg, ifiner ? ifine.n_seg : 0, out.n_seg, finer ? fine.n_seg : 0};
         L = make_layout(g->n_src, g->n_dst, E, g->ptr64 ? 8 : 4, in.n_hub, out.n_hub, segs[0], segs[2],
                         finer ? fine.n_hub : 0, segs[3], ifiner ? ifine.n_hub : 0, segs[1]);
@@ -539,7 +543,7 @@ struct Builder {
     // depend on it (partials are combined in table order).  Graphs of few
     // edges keep table order: all their segments are in flight at once.
     void build_segments(const HubArgs& H, int64_t n_seg) {
-        const bool ordered = n_seg > 0 && g->n_edges >= ORDER_EDGES;
+        const bool ordered = n_seg > 0 && g->n_edges >= order_edges();
         // 32-bit keys: ids of more than 30 bits lose their lowest ones
         const int bits = row_bits(std::max(g->n_src, g->n_dst)), id_bits = std::min(bits, 30);
         // (fewer segments than edges: an edge-sized temporary holds an array)
@@ -920,6 +924,12 @@ gnnk_status gnnk_set_option(const char* key, int64_t value) {
     } else if (k == "sddmm_split") {
         if (value < 0 || value > 8) return fail(GNNK_EINVAL, "sddmm_split is 0 (auto) or in [1, 8]");
         options().sddmm_split = value;
+    } else if (k == "order_edges") {
+        if (value < 0 || value > MAX_EDGES) return fail(GNNK_EINVAL, "order_edges is 0 (auto) or in [1, 2^31 - 2^16 - 1]");
+        options().order_edges = value;
+    } else if (k == "neighbour_lists") {
+        if (value < -1 || value > 3) return fail(GNNK_EINVAL, "neighbour_lists is -1 (auto) or in [0, 3]");
+        options().neighbour_lists = value;
     } else if (k == "no_fast") {
         if (value != 0 && value != 1) return fail(GNNK_EINVAL, "no_fast is 0 or 1");
         options().no_fast = value;

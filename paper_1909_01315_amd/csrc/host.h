@@ -86,6 +86,8 @@ struct Options {
     int64_t edge_chunk = 0; // positions per lane group of edge-parallel walks, 0 = auto
     int64_t fused_dw = -1;  // u_mul_e/sum's weight gradient inside the reverse dX pass: 1 always, 0 never, -1 one-column weights
     int64_t sddmm_split = 0;  // wavefronts per hub segment of a g-SDDMM, 0 = auto
+    int64_t order_edges = 0;  // edges from which a build orders its segments and may list rows by neighbour, 0 = auto
+    int64_t neighbour_lists = -1;  // directions listed by neighbour, where edge ids are explicit: -1 auto, else 1 in + 2 reverse
 };
 Options& options();
 

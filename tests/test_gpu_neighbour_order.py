@@ -19,22 +19,29 @@ E = (1 << 20) + 77
 S = synth.SEED_BASE + 700
 
 
-def skewed(rng, n):
-    """ids of which a tenth take nine tenths of the draws (hub rows of about E / n * 9 edges)"""
+def skewed(rng, n, hot_ids=None):
+    """ids of which a tenth (or the first hot_ids) take nine tenths of the draws"""
     a = rng.integers(0, n, E)
     hot = rng.random(E) < 0.9
-    a[hot] = rng.integers(0, max(n // 10, 1), int(hot.sum()))
+    a[hot] = rng.integers(0, hot_ids or max(n // 10, 1), int(hot.sum()))
     return a.astype(np.int32)
 
 
-@pytest.fixture(scope="module", params=["both", "in", "out"])
+# sources, destinations, their hot ones (0: none, no hub rows), the directions
+# listed; row ids of one, two and three radix digits
+GRAPHS = {"both": (3000, 2500, 300, 250, 3), "in": (300000, 2500, 0, 250, 1), "out": (3000, 300000, 300, 0, 2),
+          "one pass": (300, 400, 30, 40, 3), "three passes": (300001, 270000, 1000, 900, 3)}
+
+
+@pytest.fixture(scope="module", params=list(GRAPHS))
 def pair(request):
     rng = np.random.default_rng(11)
-    n_src, n_dst = {"both": (3000, 2500), "in": (300000, 2500), "out": (3000, 300000)}[request.param]
-    src = skewed(rng, n_src) if n_src < 300000 else rng.integers(0, n_src, E).astype(np.int32)
-    dst = skewed(rng, n_dst) if n_dst < 300000 else rng.integers(0, n_dst, E).astype(np.int32)
+    n_src, n_dst, hot_src, hot_dst, listed = GRAPHS[request.param]
+    src = skewed(rng, n_src, hot_src) if hot_src else rng.integers(0, n_src, E).astype(np.int32)
+    dst = skewed(rng, n_dst, hot_dst) if hot_dst else rng.integers(0, n_dst, E).astype(np.int32)
     p = Pair(src, dst, n_src, n_dst, ptr64=request.param == "in")
-    assert p.g.info()["identity_eids"] == 0
+    info = p.g.info()
+    assert info["identity_eids"] == 0 and info["neighbour_lists"] == listed
     return p
 
 
@@ -42,7 +49,15 @@ def test_formats_stay_in_edge_id_order(pair):
     check_formats(pair)
 
 
-def test_sums_and_their_gradients(pair):
+@pytest.fixture
+def reset_schedule():
+    yield
+    gnnk.set_option("schedule", 0)
+
+
+@pytest.mark.parametrize("schedule", [0, 2, 3])
+def test_sums_and_their_gradients(pair, schedule, reset_schedule):
+    gnnk.set_option("schedule", schedule)  # 2, 3: the edge-parallel walks
     p = pair
     X = synth.normal(S, "x", (p.o.n_src, 2, 8))
     w = synth.uniform(S, "w", (E, 2, 1), 0.5, 1.5)
@@ -113,7 +128,8 @@ def test_rows_whose_ids_lie_together_keep_their_order():
     dst = np.sort(skewed(rng, n))[::-1].copy()
     src = skewed(rng, n)
     p = Pair(src, dst, n, n)
-    assert p.g.info()["identity_eids"] == 0
+    info = p.g.info()
+    assert info["identity_eids"] == 0 and info["neighbour_lists"] == 0
     check_formats(p)
     X, w = synth.normal(S, "tx", (n, 2, 8)), synth.uniform(S, "tw", (E, 2, 1), 0.5, 1.5)
     assert_close(gnnk.gspmm(p.g, "mul", "sum", dev(X), dev(w)), orc.gspmm(p.o, "mul", "sum", X, w))
@@ -129,6 +145,7 @@ def test_from_csr_with_scattered_ids():
     o = orc.OGraph(skewed(rng, n), skewed(rng, n), n, n)
     ip, ii, ie = orc.csr(o)
     g = gnnk.Graph.from_csr(dev(ip.astype(np.int32)), dev(ii), dev(ie), n)
+    assert g.info()["neighbour_lists"] == 3
     X = synth.normal(S, "cx", (n, 1, 16))
     assert_close(gnnk.gspmm(g, "copy_lhs", "sum", dev(X)), orc.gspmm(o, "copy_lhs", "sum", X))
     dx, _ = gnnk.gspmm_backward(g, "copy_lhs", "sum", dev(X), None, dev(X))

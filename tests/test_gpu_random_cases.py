@@ -8,8 +8,9 @@ are still covered.  Each case draws
     from the in-CSR (with or without explicit edge ids);
   - library options: hub segment size, small-row threshold, schedule
     (row engine, edge-parallel ordered, edge-parallel with atomics), the
-    edge-parallel chunk, the runtime-layout kernels and the wavefronts per
-    hub segment of a g-SDDMM;
+    edge-parallel chunk, the runtime-layout kernels, the wavefronts per
+    hub segment of a g-SDDMM, segments in table order or ordered by the
+    neighbours they cover, and rows listed by neighbour in either direction;
   - shapes: H in {1, 2, 4, 8}, F from 1 to 40 (now and then a row wider than
     one pass of the wavefront: F of 100-300), each operand full (H, F), per
     head (H, 1) or one value (1, 1); fp32 or bf16; node tables with a padded
@@ -47,7 +48,7 @@ TARGETS = ["u", "e", "v"]
 def reset_options():
     yield
     for k, v in (("seg_edges", 0), ("small_deg", -1), ("schedule", 0), ("no_fast", 0), ("no_split", 0),
-                 ("edge_chunk", 0), ("sddmm_split", 0)):
+                 ("edge_chunk", 0), ("sddmm_split", 0), ("order_edges", 0), ("neighbour_lists", -1)):
         gnnk.set_option(k, v)
 
 
@@ -159,6 +160,9 @@ def test_random_case(case):
     # drawn from a stream of its own, so that the other draws of a case stay
     # those of the seed
     opts["sddmm_split"] = int(np.random.default_rng([SEED0 + case, 1]).choice([0, 0, 1, 2, 3]))
+    extra = np.random.default_rng([SEED0 + case, 2])
+    opts["order_edges"] = int(extra.choice([0, 1, 1]))
+    opts["neighbour_lists"] = int(extra.choice([-1, -1, 1, 2, 3, 3]))
     build = ["coo", "coo", "csr", "csr_eids"][int(rng.integers(4))]
     side = bool(rng.random() < 0.3)
     if rng.random() < 0.1:
@@ -194,6 +198,9 @@ def run_case(rng, src, dst, n_src, n_dst, ptr64, build, opts, H, F, bf16, kind, 
         p = CsrPair(src, dst, n_src, n_dst, ptr64, build == "csr_eids")
     E = p.o.n_edges
     rows = {"u": n_src, "e": E, "v": n_dst}
+    if opts["neighbour_lists"] >= 0:
+        info = p.g.info()
+        assert info["neighbour_lists"] == (0 if info["identity_eids"] else opts["neighbour_lists"])
 
     # g-SpMM forward and backward
     ls = kind_shape(rng, H, F) if op != "copy_rhs" else None
