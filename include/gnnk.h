@@ -140,8 +140,8 @@ typedef struct {
  * segments processed at the same time gather from one slice of the neighbour
  * table.  The order never changes a result: segment partials are combined in
  * table order (graphs of fewer than 2^20 edges keep table order).  A graph
- * of at least 2^20 edges whose edge ids are scattered over its rows, a
- * quarter of its edges in long rows, can also keep each row listed by
+ * of at least 2^20 edges whose edge ids are scattered over the rows of both
+ * CSRs, a quarter of its edges in long rows, can also keep each row listed by
  * neighbour id, and the passes that gather node rows then reduce in that
  * order, which is as fixed as the edge-id order.
  * The call synchronises `stream` once, to read back the input check and what
@@ -158,9 +158,9 @@ typedef struct {
  *    graph_destroy.  Their size is known only once the edges are sorted, so
  *    `lists` is called for them, at most once during the call, on the calling
  *    thread, and only for a graph that gains from a listing.  Listing the
- *    edges takes about as long as the rest of the build and pays after some
- *    ten passes over the graph; `lists` may be NULL, or return NULL: the
- *    graph then keeps none. */
+ *    edges takes about two thirds of the rest of the build's time and pays
+ *    after some three passes over wide rows, ten to twenty over others;
+ *    `lists` may be NULL, or return NULL: the graph then keeps none. */
 typedef struct {
     void* workspace;
     size_t workspace_bytes;

@@ -394,7 +394,7 @@ __global__ void edge_ends_kernel(const int32_t* idx, const int32_t* eid, const i
 // What the host needs to know of the sorted degrees (BuildSummary in
 // internal.h).  Workgroups 0..3: hub rows and segments of the four tables;
 // the next ones: how close a row's edge ids lie; the others: rows of more than
-// t edges, t = 0..SUMMARY_DEG, both directions.
+// t edges, t = 0..SUMMARY_DEG; both directions each.
 __device__ __forceinline__ int64_t rows_above(const uint32_t* sorted, int64_t n_rows, int64_t E, int64_t t) {
     if (t >= E) return 0;
     const uint32_t key = (uint32_t)(E - t);  // keys are E - degree, ascending
@@ -433,20 +433,18 @@ __global__ __launch_bounds__(SUMMARY_BLOCK) void summary_kernel(SummaryArgs A) {
         return;
     }
     int i = (int)(blockIdx.x - SUMMARY_TABLES) * SUMMARY_BLOCK + (int)threadIdx.x;
-    if (i < SUMMARY_SAMPLES) {
-        // evenly spaced in-CSR positions whose next edge id lies on the same
-        // or the next lines of an edge tensor
-        bool near = false;
-        if (A.eid && A.n_edges > 1) {
-            const int64_t p = (int64_t)i * (A.n_edges - 1) / SUMMARY_SAMPLES;
-            const int64_t d = (int64_t)A.eid[p + 1] - (int64_t)A.eid[p];
-            near = d >= -32 && d <= 32;
-        }
-        const uint64_t m = __ballot(near);
-        if (m != 0ull && (threadIdx.x & 63) == 0) atomicAdd(&A.out->near_ids, __popcll(m));
+    if (i < 2 * SUMMARY_SAMPLES) {
+        // evenly spaced positions whose next edge id lies on the same or the
+        // next lines of an edge tensor
+        const int d = i >= SUMMARY_SAMPLES;
+        if (!A.eid[d] || A.n_edges < 2) return;
+        const int64_t p = (int64_t)(d ? i - SUMMARY_SAMPLES : i) * (A.n_edges - 1) / SUMMARY_SAMPLES;
+        const int64_t gap = (int64_t)A.eid[d][p + 1] - (int64_t)A.eid[d][p];
+        const uint64_t m = __ballot(gap >= -32 && gap <= 32);
+        if (m != 0ull && (threadIdx.x & 63) == 0) atomicAdd(&A.out->near_ids[d], __popcll(m));
         return;
     }
-    i -= SUMMARY_SAMPLES;
+    i -= 2 * SUMMARY_SAMPLES;
     const int d = i >= SUMMARY_DEG + 1;
     const int t = d ? i - (SUMMARY_DEG + 1) : i;
     if (t > SUMMARY_DEG) return;
@@ -642,7 +640,7 @@ hipError_t launch_edge_ids(const int32_t* out_eid, int32_t* pos, const int32_t* 
 }
 
 hipError_t launch_summary(const SummaryArgs& a, hipStream_t s) {
-    const unsigned n = SUMMARY_TABLES + tiles_of(SUMMARY_SAMPLES + 2 * (SUMMARY_DEG + 1), SUMMARY_BLOCK);
+    const unsigned n = SUMMARY_TABLES + tiles_of(2 * SUMMARY_SAMPLES + 2 * (SUMMARY_DEG + 1), SUMMARY_BLOCK);
     hipLaunchKernelGGL(summary_kernel, dim3(n), dim3(SUMMARY_BLOCK), 0, s, a);
     return hipGetLastError();
 }

@@ -384,7 +384,10 @@ struct Builder {
         sa.seg_edges[2] = g->seg_edges_out;
         sa.seg_edges[3] = g->seg_edges_fine;
         sa.far[0] = sa.far[1] = in.far_deg = out.far_deg = far_degree(g);
-        sa.eid = in.eid;
+        if (E >= order_edges()) {
+            sa.eid[0] = in.eid;
+            sa.eid[1] = out.eid;
+        }
         sa.out = reinterpret_cast<BuildSummary*>(g->flag);
         chk(launch_summary(sa, s));
         BuildSummary sum;
@@ -421,9 +424,10 @@ struct Builder {
             fine.n_hub = sum.n_hub[3];
             fine.n_seg = sum.n_seg[3];
         }
-        const bool local_ids = 2 * sum.near_ids >= SUMMARY_SAMPLES;
+        // (the rule and its figures: list_by_neighbour)
+        const bool scattered = 2 * std::max(sum.near_ids[0], sum.near_ids[1]) < SUMMARY_SAMPLES;
         auto worth = [&](const Dir& f, int64_t S) {
-            return in.eid && !local_ids && E >= order_edges() && 4 * f.n_seg * S >= E;
+            return in.eid && scattered && E >= order_edges() && 4 * f.n_seg * S >= E;
         };
         bool nbr_in = worth(ifine, g->seg_edges_in_fine), nbr_out = worth(fine, g->seg_edges_fine);
         if (const int64_t o = options().neighbour_lists; o >= 0) {
@@ -516,11 +520,28 @@ struct Builder {
     // edge ids, are as scattered in either order.  114.6M edges in arrival
     // order, 128 columns: the fused attention forward 7.26 -> 3.95 ms and the
     // two passes of its backward 7.23 + 7.22 -> 3.83 + 5.88 ms; 61.9M edges,
-    // 100 columns: the mean 4.10 -> 3.35 ms and its gradient 5.13 -> 3.98 ms;
-    // the build of those graphs 9.6 -> 16.9 ms and 6.1 -> 12.4 ms.
-    // Where the ids of a row lie together, the operands would lose more than
-    // the gathers gain, and where few edges lie in hub rows there is nothing
-    // to gain: those graphs are left as they are.
+    // 100 columns: the mean 4.10 -> 3.35 ms and its gradient 5.13 -> 3.98 ms.
+    // The build takes 3 ms more on 60M edges and 1.4 ms on 20M.
+    //
+    // A graph keeps such listings where at most half of the sampled edge ids
+    // of either direction's rows lie next to each other.  60M edges, listed
+    // against not: a list of shuffled pairs of neighbours, half of them
+    // together, 8 x 16: u_mul_e/sum 3.51 -> 2.43 ms, its backward 7.24 ->
+    // 4.82, u_dot_v 3.22 -> 2.02.  A list grouped by destination, the groups
+    // in another order, reads its edge tensors in sequence and loses where
+    // rows are narrow: 1 x 16: u_mul_e/sum 0.62 -> 0.84, u_dot_v 0.61 -> 0.98;
+    // 8 x 2: 1.29 -> 1.52 and 1.53 -> 2.47.  A list sorted by source has its
+    // in-rows in neighbour order as they are (nothing gained) and its reverse
+    // rows' ids together: u_mul_e/sum backward, 8 x 2: 3.38 -> 3.76.  (Rows of
+    // 128 columns and passes without an edge operand gain on such lists too,
+    // the mean's gradient on the last 3.34 -> 1.75 with destinations in random
+    // order; they run in edge-id order all the same.)
+    // And where a direction's hub segments hold a quarter of its edges: 20M
+    // edges on 1M nodes with a tenth, a quarter, half and nine tenths of them
+    // there, 8 x 16: the mean 1.50 -> 1.43, 1.31 -> 1.23, 1.08 -> 1.01 and
+    // 0.80 -> 0.65 ms, u_dot_v 2.30 -> 2.27, 2.14 -> 2.00, 1.86 -> 1.58 and
+    // 1.33 -> 1.12: at a tenth a listing pays after some 25 passes, at a
+    // quarter after 10 to 18.
     void list_by_neighbour(bool nbr_in, bool nbr_out) {
         auto u = [](const int32_t* p) { return const_cast<uint32_t*>(reinterpret_cast<const uint32_t*>(p)); };
         auto list_by = [&](int d, const Dir& other, int64_t n_rows, Dir& by) {

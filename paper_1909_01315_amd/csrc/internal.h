@@ -321,7 +321,7 @@ constexpr int SUMMARY_TABLES = 4;
 constexpr int SUMMARY_SAMPLES = 16384;
 struct BuildSummary {
     int32_t flag;
-    int32_t near_ids;                     // of SUMMARY_SAMPLES in-CSR positions: next id within 32 of theirs
+    int32_t near_ids[2];                  // of SUMMARY_SAMPLES positions: next edge id within 32 of theirs
     int32_t n_hub[SUMMARY_TABLES], n_seg[SUMMARY_TABLES];
     int32_t max_deg[2];
     int32_t above_far[2];                 // rows of more than SummaryArgs::far edges
@@ -333,8 +333,8 @@ struct SummaryArgs {
     int64_t n_edges;
     int64_t seg_edges[SUMMARY_TABLES];
     int64_t far[2];
-    const int32_t* eid;  // the in-CSR's edge ids, nullptr: identity
-    BuildSummary* out;   // its flag and near_ids zeroed beforehand
+    const int32_t* eid[2];  // edge ids by position, nullptr: not sampled
+    BuildSummary* out;      // its flag and near_ids zeroed beforehand
 };
 hipError_t launch_summary(const SummaryArgs& a, hipStream_t s);
 // the hub tables of a graph: offsets and segments (with the sort keys of the

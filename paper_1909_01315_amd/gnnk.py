@@ -294,8 +294,9 @@ class Graph:
                  stream=None, neighbour_lists: bool = True) -> "Graph":
         """The graph of an edge list.  neighbour_lists: whether a graph that
         gains from it may also list its rows by neighbour (8 bytes per edge
-        and direction, and about the time of the build once more, which pays
-        after some ten passes over the graph)."""
+        and direction, and two thirds of the build's time once more, which
+        pays after some three passes over wide rows, ten to twenty over
+        others)."""
         assert src.dtype == torch.int32 and dst.dtype == torch.int32 and src.is_cuda and dst.is_cuda
         src, dst = src.contiguous(), dst.contiguous()
         ptr_t = I64 if ptr64 else I32

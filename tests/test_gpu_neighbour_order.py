@@ -28,9 +28,10 @@ def skewed(rng, n, hot_ids=None):
 
 
 # sources, destinations, their hot ones (0: none, no hub rows), the directions
-# listed; row ids of one, two and three radix digits
+# listed; row ids of one, two and three radix digits.  (A row of E / 33 edges
+# or more would have its ids next to each other by chance alone.)
 GRAPHS = {"both": (3000, 2500, 300, 250, 3), "in": (300000, 2500, 0, 250, 1), "out": (3000, 300000, 300, 0, 2),
-          "one pass": (300, 400, 30, 40, 3), "three passes": (300001, 270000, 1000, 900, 3)}
+          "one pass": (300, 400, 100, 120, 3), "three passes": (300001, 270000, 1000, 900, 3)}
 
 
 @pytest.fixture(scope="module", params=list(GRAPHS))
@@ -134,6 +135,27 @@ def test_rows_whose_ids_lie_together_keep_their_order():
     X, w = synth.normal(S, "tx", (n, 2, 8)), synth.uniform(S, "tw", (E, 2, 1), 0.5, 1.5)
     assert_close(gnnk.gspmm(p.g, "mul", "sum", dev(X), dev(w)), orc.gspmm(p.o, "mul", "sum", X, w))
     dZ = synth.normal(S, "tz", (n, 2, 8))
+    for x, y in zip(gnnk.gspmm_backward(p.g, "mul", "sum", dev(X), dev(w), dev(dZ)),
+                    orc.gspmm_backward(p.o, "mul", "sum", X, w, dZ)):
+        assert_close(x, y)
+
+
+@pytest.mark.parametrize("order", ["by source", "by source and destination", "by source, destinations descending"])
+def test_edge_lists_sorted_by_source_keep_their_order(order):
+    """The in-rows list their neighbours in order as they are, and the edge
+    ids of a reverse row lie together."""
+    rng = np.random.default_rng(6)
+    n = 20000
+    src, dst = skewed(rng, n), skewed(rng, n)
+    second = rng.random(E) if order == "by source" else (-dst if "descending" in order else dst)
+    at = np.lexsort((second, src))
+    src, dst = src[at], dst[at]
+    p = Pair(src, dst, n, n)
+    info = p.g.info()
+    assert info["identity_eids"] == 0 and info["neighbour_lists"] == 0
+    check_formats(p)
+    X, w, dZ = (synth.normal(S, k, sh) for k, sh in (("sx", (n, 2, 8)), ("sw", (E, 2, 1)), ("sz", (n, 2, 8))))
+    assert_close(gnnk.gspmm(p.g, "mul", "sum", dev(X), dev(w)), orc.gspmm(p.o, "mul", "sum", X, w))
     for x, y in zip(gnnk.gspmm_backward(p.g, "mul", "sum", dev(X), dev(w), dev(dZ)),
                     orc.gspmm_backward(p.o, "mul", "sum", X, w, dZ)):
         assert_close(x, y)
