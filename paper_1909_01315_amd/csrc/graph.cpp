@@ -875,6 +875,9 @@ gnnk_status graph_validate(gnnk_graph_t g, hipStream_t stream) {
     if (e == hipSuccess) e = launch_validate_ptr(g->out.ptr, g->ptr64, g->n_src, E, g->flag, stream);
     if (e == hipSuccess) e = launch_validate(g->in.idx, g->n_src, g->out.idx, g->n_dst, E, g->flag, stream);
     if (e == hipSuccess) e = launch_validate(g->out.eid, E, g->in.eid, E, E, g->flag, stream);
+    if (e == hipSuccess && g->listed)
+        e = launch_validate(g->in_nbr.idx, g->n_src, g->out_nbr.idx, g->n_dst, E, g->flag, stream);
+    if (e == hipSuccess && g->listed) e = launch_validate(g->out_nbr.eid, E, g->in_nbr.eid, E, E, g->flag, stream);
     int32_t h = 0;
     if (e == hipSuccess) e = hipMemcpyAsync(&h, g->flag, 4, hipMemcpyDeviceToHost, stream);
     if (e == hipSuccess) e = hipStreamSynchronize(stream);

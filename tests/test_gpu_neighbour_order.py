@@ -161,6 +161,28 @@ def test_edge_lists_sorted_by_source_keep_their_order(order):
         assert_close(x, y)
 
 
+def test_validate_reads_the_listings():
+    rng = np.random.default_rng(9)
+    n = 2000
+    p = Pair(skewed(rng, n), skewed(rng, n), n, n)
+    info = p.g.info()
+    assert info["neighbour_lists"] == 3
+    p.g.validate()
+    lists = p.g._keep[1]
+    assert lists.numel() == info["lists_bytes"]
+    words = lists[: lists.numel() // 4 * 4].view(torch.int32)
+    # four arrays of E words each, 256 bytes aligned, the segment orders of a
+    # direction after its two
+    for at in (E - 1, -(-E // 64) * 64 + E - 1):
+        kept = int(words[at])
+        words[at] = 1 << 30
+        with pytest.raises(gnnk.GnnkError) as err:
+            p.g.validate()
+        assert err.value.status == gnnk.ERANGE
+        words[at] = kept
+    p.g.validate()
+
+
 def test_from_csr_with_scattered_ids():
     rng = np.random.default_rng(8)
     n = 2000
