@@ -56,15 +56,18 @@ int pow2ceil(int x) {
 // per-head scores have the shape of a full operand).
 //
 // Vectors: the widest of 8 (bf16), 4, 2 and 1 columns that divides F, at the
-// elements' own alignment.  Where that is less than four and overlap is
-// allowed, four (fp32) or eight (bf16), a head's
-// last vector overlapping the one before it: rows of 47 columns take 12 lanes
+// elements' own alignment.  Where that is less than four, F holds a vector of
+// four (fp32) or eight (bf16), the rows are no wider than 65,536 columns, the
+// walks are the row engine's (see below) and the pass allows it (winner masks
+// and edge softmax do not), such vectors are taken all the same, a head's last
+// one overlapping the one before it: rows of 47 columns take 12 lanes
 // of 16 (bf16: 6 of 8) and the compile-time layouts instead of 47 of 64 and
 // the runtime ones.  8.4M edges from 262,144 nodes, 47 columns, mean forward
-// and backward: fp32 796 -> 730 us (bound by the lines its rows touch, 2.5 of
-// 128 bytes each), bf16 828 -> 507; the u_dot_v step 1862 -> 1284; 640,000
-// edges, 3 heads of 45, fused attention step 852 -> 172.  The choice depends
-// on F and the type alone, so every pass of a call makes the same one.
+// and backward: fp32 809 -> 735 us (bound by the lines its rows touch, 2.5 of
+// 128 bytes each), bf16 828 -> 509; the u_dot_v step 1862 -> 1294; 640,000
+// edges, 3 heads of 45, fused attention step 852 -> 179.  A walk and its
+// combine share one geometry; the passes of a call need not (they exchange
+// tensors, winner bits by column and records by head).
 gnnk_status choose_geo(int Hm, int Fm, std::vector<Member>& ms, Geo& g, bool keep_heads = false,
                        bool overlap = true) {
     for (auto& m : ms) {

@@ -64,7 +64,7 @@ struct RsJob {
     const uint32_t* key;
     const uint32_t* v0;  // nullptr: 0..n-1
     const uint32_t* v1;
-    uint32_t* key_out;   // nullptr: the sorted keys are dropped
+    uint32_t* key_out;
     uint32_t* out0;
     uint32_t* out1;
     int64_t n;
@@ -217,7 +217,7 @@ __global__ __launch_bounds__(RS_BLOCK) void rs_scatter_kernel(RsArgs A) {
         if (i < m) {
             const uint32_t key = stage[i];
             to[j] = first[(key >> shift) & mask] + (uint32_t)i;
-            if (J.key_out) J.key_out[to[j]] = key;
+            J.key_out[to[j]] = key;
         }
     }
     auto put = [&](const uint32_t* v, uint32_t* out) {
@@ -537,6 +537,9 @@ int key_bits(uint64_t max_key) { return max_key == 0 ? 0 : 64 - __builtin_clzll(
 
 namespace {
 
+// passes of a sort by `bits` bits; they write out and tmp in turn, the last one out
+int radix_passes(int bits) { return std::max(1, (bits + RS_BITS - 1) / RS_BITS); }
+
 int rs_steps(int64_t n) { return n <= (int64_t)RS_DIRECT * rs_tile(4) ? 4 : 16; }
 
 hipError_t scan_exclusive_u32(uint32_t* x, int64_t n, uint32_t* part, hipStream_t s) {
@@ -558,8 +561,6 @@ size_t radix_scratch_words(int64_t n0, int64_t n1) {
     return (size_t)(hist + tiles_of(hist, SCAN_TILE) + 64);
 }
 
-int radix_passes(int bits) { return std::max(1, (bits + RS_BITS - 1) / RS_BITS); }
-
 hipError_t radix_sort(const RadixSort* sorts, int n_sorts, uint32_t* scratch, hipStream_t s) {
     int64_t most = 0;
     int passes = 1;
@@ -574,7 +575,6 @@ hipError_t radix_sort(const RadixSort* sorts, int n_sorts, uint32_t* scratch, hi
     for (int q = 0; q < n_sorts; ++q) src[q] = sorts[q].in;
     const bool two = sorts[0].in.v1 != nullptr;
     for (int pass = 0; pass < passes; ++pass) {
-        const bool last = pass == passes - 1;
         RsArgs A{};
         A.hist = scratch;
         int64_t words = 0, before = 0, tiles = 0;
@@ -593,7 +593,6 @@ hipError_t radix_sort(const RadixSort* sorts, int n_sorts, uint32_t* scratch, hi
             J.key_out = dst.key;
             J.out0 = dst.v0;
             J.out1 = dst.v1;
-            if (last) J.key_out = R.out.key;
             J.n = R.n;
             J.n_tiles = (int32_t)tiles_of(R.n, rs_tile(steps));
             J.shift = shift[q];

@@ -552,8 +552,8 @@ template <int VEC, bool OV>
 __device__ __forceinline__ Cols cols_of(const GeomDev& geo, bool active, int j) {
     j = active ? j : 0;
     if constexpr (!OV) return Cols{j * VEC, j * VEC / geo.F, 0};
-    // h = j / FV: a multiplication (rows of overlapping vectors have at most
-    // 2^14 of them)
+    // h = j / FV: a multiplication, exact while 2 NV FV < 2^31 (rows of
+    // overlapping vectors have at most 65,536 columns: at most 2^29)
     const int h = (int)__umulhi(2u * (uint32_t)j + 1u, geo.fv_magic);
     const int at = j * VEC - h * geo.ov, last = h * geo.F + geo.F - VEC;
     return Cols{at < last ? at : last, h, at > last ? geo.ov : 0};

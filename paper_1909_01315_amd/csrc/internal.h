@@ -104,7 +104,7 @@ struct GeomDev {
     int32_t FV;      // vectors per head (NV = heads * FV)
     int32_t ov;      // columns of a head's last vector that the one before it holds too
     int32_t D;       // columns per message row
-    uint32_t fv_magic;  // 2^31 / FV rounded up: (2 j + 1) * fv_magic / 2^32 is j / FV while NV <= 2^14
+    uint32_t fv_magic;  // 2^31 / FV rounded up: (2 j + 1) * fv_magic / 2^32 is j / FV while 2 NV FV < 2^31
 };
 
 // flags of a row-engine call
@@ -284,17 +284,13 @@ struct RadixArrays {
 };
 // A stable sort of n keys and their values by the low `bits` bits of the key.
 // in is only read (in.v0 == nullptr stands for 0..n-1); the result lands in
-// out, whose key may be nullptr where the sort takes at most two passes of 9
-// bits; tmp (n entries each, used from two passes on) is clobbered.  No
-// array may alias another (an input array may serve as one that is written in
-// the second pass or later).
+// out; tmp (n entries each, used from two passes on) is clobbered.  No array
+// may alias another.
 struct RadixSort {
     RadixArrays in, out, tmp;
     int64_t n;
     int bits;
 };
-// passes of a sort by `bits` bits; they write out and tmp in turn, the last one out
-int radix_passes(int bits);
 // uint32 words of scratch radix_sort needs for sorts of n0 and n1 keys
 size_t radix_scratch_words(int64_t n0, int64_t n1);
 // one or two such sorts (of the same number of arrays) in the same launches
