@@ -49,44 +49,20 @@ int pow2ceil(int x) {
     return p;
 }
 
-// Choose the canonical geometry of an (Hm, Fm) message read and written by
-// `ms`.  When no tensor broadcasts over features only, heads and features
-// merge into one row of Hm * Fm columns, unless keep_heads (a kernel that
-// needs each lane's head, as the fused attention does; with Fm = 1 its
-// per-head scores have the shape of a full operand).
-//
-// Vectors: the widest of 8 (bf16), 4, 2 and 1 columns that divides F, at the
-// elements' own alignment.  Where that is less than four, F holds a vector of
-// four (fp32) or eight (bf16), the rows are no wider than 65,536 columns, the
-// walks are the row engine's (see below) and the pass allows it (winner masks
-// and edge softmax do not), such vectors are taken all the same, a head's last
-// one overlapping the one before it: rows of 47 columns take 12 lanes
-// of 16 (bf16: 6 of 8) and the compile-time layouts instead of 47 of 64 and
-// the runtime ones.  8.4M edges from 262,144 nodes, 47 columns, mean forward
-// and backward: fp32 809 -> 735 us (bound by the lines its rows touch, 2.5 of
-// 128 bytes each), bf16 828 -> 509; the u_dot_v step 1862 -> 1294; 640,000
-// edges, 3 heads of 45, fused attention step 852 -> 179.  A walk and its
-// combine share one geometry; the passes of a call need not (they exchange
-// tensors, winner bits by column and records by head).
-gnnk_status choose_geo(int Hm, int Fm, std::vector<Member>& ms, Geo& g, bool keep_heads = false,
-                       bool overlap = true) {
-    for (auto& m : ms) {
-        m.kind = kind_of(m.t, Hm, Fm);
-        if (m.kind == K_BAD)
-            return fail(GNNK_EINVAL, "tensor (%d, %d) does not broadcast against the (%d, %d) message", m.t->heads,
-                        m.t->feat, Hm, Fm);
-    }
-    bool any_heads = false;
-    for (auto& m : ms) any_heads = any_heads || (m.kind == K_HEADS);
-    g.merged = !any_heads && !keep_heads;
-    g.H = g.merged ? 1 : Hm;
-    g.F = g.merged ? Hm * Fm : Fm;
-    g.D = (int64_t)Hm * Fm;
-    const int es = ms.empty() ? 4 : (ms[0].t->dtype == GNNK_BF16 ? 2 : 4);
-    g.vec = es == 2 && g.F % 8 == 0 ? 8 : (g.F % 4 == 0 ? 4 : (g.F % 2 == 0 ? 2 : 1));
-    // (the edge-parallel walks would add the shared columns twice)
-    const int wide = es == 2 ? 8 : 4;
-    if (overlap && g.vec < 4 && g.F >= wide && options().schedule < 2 && g.D <= 65536) g.vec = wide;
+// Which rows a pass overlaps vectors on (where no vector of four columns
+// divides them): by what it moves per edge.
+enum class Overlap {
+    NONE,
+    SUMMED,    // one value per edge and head out of a row, or none: dots, fused attention, winner masks
+    GATHERED,  // rows of nodes alone, summed or written per edge
+    EDGES      // an edge tensor beside them, or rows of edges; max and min
+};
+
+// the widest vector that divides F columns
+int exact_vec(int F, int es) { return es == 2 && F % 8 == 0 ? 8 : (F % 4 == 0 ? 4 : (F % 2 == 0 ? 2 : 1)); }
+
+// vectors, lanes and lane groups of rows of g.vec columns a vector
+void set_lanes(Geo& g) {
     g.FV = (g.F + g.vec - 1) / g.vec;
     g.ov = g.FV * g.vec - g.F;
     g.NV = g.H * g.FV;
@@ -100,6 +76,64 @@ gnnk_status choose_geo(int Hm, int Fm, std::vector<Member>& ms, Geo& g, bool kee
     g.log2L = 0;
     while ((1 << g.log2L) < g.L) ++g.log2L;
     g.G = 64 / g.L;
+}
+
+// Choose the canonical geometry of an (Hm, Fm) message read and written by
+// `ms`.  When no tensor broadcasts over features only, heads and features
+// merge into one row of Hm * Fm columns, unless keep_heads (a kernel that
+// needs each lane's head, as the fused attention does; with Fm = 1 its
+// per-head scores have the shape of a full operand).
+//
+// Vectors: the widest of 8 (bf16), 4, 2 and 1 columns that divides F, at the
+// elements' own alignment.  Where that is less than four, F holds a vector of
+// four (fp32) or eight (bf16), the rows are no wider than 65,536 columns, the
+// walks are the row engine's (see below) and the rule here says so, such
+// vectors are taken all the same, a head's last one overlapping the one before
+// it: rows of 47 columns take 12 lanes of 16 (bf16: 6 of 8) and the
+// compile-time layouts instead of 47 of 64 and the runtime ones.  8.4M edges
+// from 262,144 nodes, 47 columns, mean forward and backward: fp32 809 -> 735 us
+// (bound by the lines its rows touch, 2.5 of 128 bytes each), bf16 828 -> 509;
+// the u_dot_v step 1862 -> 1294; 640,000 edges, 3 heads of 45, fused attention
+// step 852 -> 179.  A walk and its combine need not share vectors, nor the
+// passes of a call (they exchange partials and winner bits by column, tensors
+// and records by head).
+//
+// Narrow rows lose by it: a row's work lies in few lanes, which also load the
+// shared columns.  Exact -> overlapping vectors, us, on 1M edges of degree 20,
+// 6M skewed ones and 8.4M of degree 32.  Passes that sum a row's columns, from
+// nine lanes of exact vectors: u_dot_v fp32, 7 columns 24 -> 28, 110 -> 109,
+// 146 -> 171; 9 columns 33 -> 28, 180 -> 121, 226 -> 165.  So too fp32 rows of
+// nodes alone: mean, 10 columns (5 lanes) 13 -> 12, 103 -> 87, 97 -> 142; 9
+// columns 16 -> 12, 113 -> 86, 117 -> 135.  The others, and those in bf16 (8
+// columns a lane), from 17 columns: u_mul_e/sum fp32, 13 columns 17 -> 20,
+// 120 -> 106, 159 -> 197; 17 columns 27 -> 19, 166 -> 113, 186 -> 198; mean
+// bf16, 13 columns 15 -> 15, 113 -> 135, 93 -> 104; 17 columns 24 -> 16,
+// 163 -> 147, 157 -> 127.  Above these lines overlapping gains up to 3 times
+// on most graphs and loses where every row has 32 edges: mean fp32 of 18-30
+// columns 158 -> 190 (21 -> 15 and 139 -> 103 on the other two); and in the
+// gradients of a sum per edge, 17-31 columns: 57 -> 66 on the first graph.
+gnnk_status choose_geo(int Hm, int Fm, std::vector<Member>& ms, Geo& g, Overlap rule, bool keep_heads = false) {
+    for (auto& m : ms) {
+        m.kind = kind_of(m.t, Hm, Fm);
+        if (m.kind == K_BAD)
+            return fail(GNNK_EINVAL, "tensor (%d, %d) does not broadcast against the (%d, %d) message", m.t->heads,
+                        m.t->feat, Hm, Fm);
+    }
+    bool any_heads = false;
+    for (auto& m : ms) any_heads = any_heads || (m.kind == K_HEADS);
+    g.merged = !any_heads && !keep_heads;
+    g.H = g.merged ? 1 : Hm;
+    g.F = g.merged ? Hm * Fm : Fm;
+    g.D = (int64_t)Hm * Fm;
+    const int es = ms.empty() ? 4 : (ms[0].t->dtype == GNNK_BF16 ? 2 : 4);
+    g.vec = exact_vec(g.F, es);
+    // (the edge-parallel walks would add the shared columns twice)
+    const int wide = es == 2 ? 8 : 4;
+    const bool by_lanes = rule == Overlap::SUMMED || (rule == Overlap::GATHERED && es == 4);
+    const bool enough = by_lanes ? g.H * (g.F / g.vec) > 8 : g.D > 16;
+    if (rule != Overlap::NONE && enough && g.vec < 4 && g.F >= wide && options().schedule < 2 && g.D <= 65536)
+        g.vec = wide;
+    set_lanes(g);
     return GNNK_OK;
 }
 
@@ -436,10 +470,10 @@ gnnk_tensor head_slice(const gnnk_tensor* t, int Hm, int h0, int hc) {
 // per head of an (Hm, Fm) message, Fm > 1) that would need more than one pass
 // of the wavefront: Fm / vec lanes per head, 64 lanes per pass; one head per
 // slice when a head alone is wider (its sum then runs over several passes).
-// 0: the call runs whole.  overlap: whether every pass of the call may overlap
-// vectors.
+// 0: the call runs whole.  rule: Overlap::NONE where a pass of the call may not
+// overlap vectors (rows of more than one pass overlap under any other).
 int heads_per_slice(int Hm, int Fm, std::initializer_list<const gnnk_tensor*> all,
-                    std::initializer_list<const gnnk_tensor*> outs, bool overlap = true) {
+                    std::initializer_list<const gnnk_tensor*> outs, Overlap rule = Overlap::EDGES) {
     if (Hm <= 1 || Fm <= 1) return 0;
     bool per_head = false;
     for (const gnnk_tensor* t : outs)
@@ -449,7 +483,7 @@ int heads_per_slice(int Hm, int Fm, std::initializer_list<const gnnk_tensor*> al
     for (const gnnk_tensor* t : all)
         if (t) ms.push_back({t, K_FULL});
     Geo geo;
-    if (choose_geo(Hm, Fm, ms, geo, false, overlap) != GNNK_OK || geo.merged || geo.nchunk == 1) return 0;
+    if (choose_geo(Hm, Fm, ms, geo, rule) != GNNK_OK || geo.merged || geo.nchunk == 1) return 0;
     return std::max(1, 64 / geo.FV);
 }
 
@@ -484,7 +518,7 @@ gnnk_status gspmm_impl(gnnk_graph_t g, gnnk_binop op, gnnk_reduce reduce, const 
     if (use_r) ms.push_back({rhs, K_FULL});
     ms.push_back({out, K_FULL});
     Geo geo;
-    gnnk_status st = choose_geo(Hm, Fm, ms, geo);
+    gnnk_status st = choose_geo(Hm, Fm, ms, geo, use_r || cmp ? Overlap::EDGES : Overlap::GATHERED);
     if (st != GNNK_OK) return st;
     if (g->n_dst == 0) return GNNK_OK;
     EngineArgs A{};
@@ -522,8 +556,17 @@ gnnk_status gspmm_impl(gnnk_graph_t g, gnnk_binop op, gnnk_reduce reduce, const 
     }
     const Pick pk = pick_spmm(g, d, A, geo, dtype_code(out), opk, true);
     st = GNNK_LAUNCH(launch_spmm(A, dtype_code(out), geo.vec, true, opk, pk.spec, pk.gc, stream), "g-SpMM launch");
-    if (st == GNNK_OK && A.sch.n_hub > 0)
+    if (st == GNNK_OK && A.sch.n_hub > 0) {
+        // with exact vectors: three arrays of partials in a few lanes' chains
+        // took the combine of 6M skewed edges, 9-33 bf16 columns, from about
+        // 100 us to 350
+        if (geo.ov) {
+            geo.vec = exact_vec(geo.F, out->dtype == GNNK_BF16 ? 2 : 4);
+            set_lanes(geo);
+            set_geo(A, geo);
+        }
         st = GNNK_LAUNCH(launch_spmm_combine(A, dtype_code(out), geo.vec, true, stream), "g-SpMM combine launch");
+    }
     return st;
 }
 
@@ -635,7 +678,9 @@ gnnk_status gsddmm(gnnk_graph_t g, gnnk_binop op, const gnnk_tensor* lhs, gnnk_t
     if (use_r) ms.push_back({rhs, K_FULL});
     ms.push_back({out, K_FULL});
     Geo geo;
-    gnnk_status st = choose_geo(Hm, Fm, ms, geo);
+    const bool edges = (use_l && lhs_target == GNNK_EDGE) || (use_r && rhs_target == GNNK_EDGE);
+    gnnk_status st = choose_geo(Hm, Fm, ms, geo, edges ? Overlap::EDGES
+                                                       : (op == GNNK_DOT ? Overlap::SUMMED : Overlap::GATHERED));
     if (st != GNNK_OK) return st;
     if (g->n_edges == 0) return GNNK_OK;
     EngineArgs A{};
@@ -687,7 +732,8 @@ static gnnk_status spmm_backward(gnnk_graph_t g, gnnk_binop op, gnnk_reduce redu
     if (grad_rhs && (grad_rhs->rows != g->n_edges || grad_rhs->heads != rhs->heads || grad_rhs->feat != rhs->feat))
         return fail(GNNK_EINVAL, "grad_rhs must have rhs's shape");
     const int64_t ld = arg_ld >= 0 ? arg_ld : (int64_t)Hm * Fm;
-    if (const int hs = heads_per_slice(Hm, Fm, {lhs, rhs, grad_out, grad_lhs, grad_rhs}, {grad_lhs, grad_rhs}, !cmp)) {
+    if (const int hs = heads_per_slice(Hm, Fm, {lhs, rhs, grad_out, grad_lhs, grad_rhs}, {grad_lhs, grad_rhs},
+                                     cmp ? Overlap::NONE : Overlap::EDGES)) {
         // per-head gradients wider than one pass: slices of heads, one call each
         for (int h0 = 0; h0 < Hm; h0 += hs) {
             const int hc = std::min(hs, Hm - h0);
@@ -714,11 +760,12 @@ static gnnk_status spmm_backward(gnnk_graph_t g, gnnk_binop op, gnnk_reduce redu
         if (op == GNNK_MUL || op == GNNK_DIV) ms.push_back({rhs, K_FULL});
         ms.push_back({grad_lhs, K_FULL});
         Geo geo;
-        gnnk_status st = choose_geo(Hm, Fm, ms, geo);
+        gnnk_status st = choose_geo(Hm, Fm, ms, geo, cmp ? Overlap::SUMMED
+                                                         : (ms.size() > 2 ? Overlap::EDGES : Overlap::GATHERED));
         // winner masks: a vector's bits lie in one 32-bit word, so no overlap
         // of heads' vectors, nor of a row's last one into the word before
         if (st == GNNK_OK && cmp && geo.ov && (!geo.merged || (geo.D % 32 != 0 && geo.D % 32 < geo.vec)))
-            st = choose_geo(Hm, Fm, ms, geo, false, false);
+            st = choose_geo(Hm, Fm, ms, geo, Overlap::NONE);
         if (st != GNNK_OK) return st;
         EngineArgs A{};
         A.a = operand(grad_out, ms[0].kind, T_NBR);
@@ -811,7 +858,9 @@ static gnnk_status spmm_backward(gnnk_graph_t g, gnnk_binop op, gnnk_reduce redu
         if (op == GNNK_DIV) ms.push_back({rhs, K_FULL});
         ms.push_back({grad_rhs, K_FULL});
         Geo geo;
-        gnnk_status st = choose_geo(Hm, Fm, ms, geo);
+        // (a gradient per head or edge is a dot; a whole row is written)
+        const bool dots = grad_rhs->feat < Fm || grad_rhs->heads < Hm;
+        gnnk_status st = choose_geo(Hm, Fm, ms, geo, dots ? Overlap::SUMMED : Overlap::EDGES);
         if (st != GNNK_OK) return st;
         EngineArgs A{};
         A.a = operand(grad_out, ms[0].kind, T_SELF);
@@ -941,7 +990,7 @@ static gnnk_status sddmm_backward(gnnk_graph_t g, gnnk_binop op, const gnnk_tens
         if (ct) ms.push_back({ct, K_FULL});
         ms.push_back({gx, K_FULL});
         Geo geo;
-        gnnk_status st = choose_geo(Hm, Fm, ms, geo);
+        gnnk_status st = choose_geo(Hm, Fm, ms, geo, Overlap::EDGES);
         if (st != GNNK_OK) return st;
         if (swap) {
             A.a = operand(bt, ms[0].kind, tg(b_target));
@@ -988,7 +1037,7 @@ static gnnk_status softmax_common(gnnk_graph_t g, const gnnk_tensor* a, const gn
     std::vector<Member> ms{{a, K_FULL}, {out, K_FULL}};
     if (b) ms.push_back({b, K_FULL});
     Geo geo;
-    gnnk_status st = choose_geo(a->heads, a->feat, ms, geo, false, false);
+    gnnk_status st = choose_geo(a->heads, a->feat, ms, geo, Overlap::NONE);
     if (st != GNNK_OK) return st;
     if (g->n_edges == 0) return GNNK_OK;
     EngineArgs A{};
@@ -1042,7 +1091,7 @@ gnnk_status gat_aggregate(gnnk_graph_t g, const gnnk_tensor* feat, const gnnk_te
     // el and er broadcast over features: keep heads separate (F per head)
     std::vector<Member> ms{{feat, K_FULL}, {el, K_FULL}, {out, K_FULL}};
     Geo geo;
-    gnnk_status st = choose_geo(H, F, ms, geo, true);
+    gnnk_status st = choose_geo(H, F, ms, geo, Overlap::SUMMED, true);
     if (st != GNNK_OK) return st;
     if (g->n_dst == 0) return GNNK_OK;
     EngineArgs A{};
@@ -1088,7 +1137,7 @@ static gnnk_status gat_bwd_run(gnnk_graph_t g, const gnnk_tensor* feat, const gn
     const int H = feat->heads, F = feat->feat;
     std::vector<Member> ms{{feat, K_FULL}, {el, K_FULL}, {grad_out, K_FULL}};
     Geo geo;
-    gnnk_status st = choose_geo(H, F, ms, geo, true);
+    gnnk_status st = choose_geo(H, F, ms, geo, Overlap::SUMMED, true);
     if (st != GNNK_OK) return st;
     if (geo.nchunk != 1) return fail(GNNK_EUNSUPPORTED, "fused attention backward: a slice wider than one pass");
     const int dt = dtype_code(grad_out);
@@ -1175,7 +1224,7 @@ static gnnk_status gat_backward(gnnk_graph_t g, const gnnk_tensor* feat, const g
         return fail(GNNK_EINVAL, "each gradient must have its operand's shape");
     std::vector<Member> ms{{feat, K_FULL}, {el, K_FULL}, {grad_out, K_FULL}};
     Geo geo;
-    gnnk_status st = choose_geo(H, F, ms, geo, true);
+    gnnk_status st = choose_geo(H, F, ms, geo, Overlap::SUMMED, true);
     if (st != GNNK_OK) return st;
     Scratch sc = scratch_of(g, stream);
     if (geo.nchunk == 1) {

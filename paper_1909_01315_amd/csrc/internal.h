@@ -191,7 +191,7 @@ hipError_t launch_spmm_combine(const EngineArgs& a, int dtype, int vec, bool max
 // the same for rows whose vectors overlap (spmm_ov.hip)
 hipError_t launch_spmm_ov(const EngineArgs& a, int dtype, bool maxmin, int opk, int spec, int gc, dim3 grid,
                           dim3 block, hipStream_t s);
-hipError_t launch_spmm_combine_ov(const EngineArgs& a, int dtype, bool maxmin, dim3 grid, dim3 block, hipStream_t s);
+hipError_t launch_spmm_combine_ov(const EngineArgs& a, int dtype, dim3 grid, dim3 block, hipStream_t s);
 // edge-parallel (COO) walks, edge.hip: mode 0 = partials of split rows combined
 // in order afterwards, mode 1 = fp64 atomics into scratch (a.partial, rows x D)
 hipError_t launch_spmm_edge(const EngineArgs& a, int64_t n_pos, int64_t n_rows, int dtype, int vec, int opk, int spec,

@@ -78,11 +78,11 @@ hipError_t launch_spmm_combine(const EngineArgs& a, int dtype, int vec, bool max
     if (a.sch.n_hub <= 0) return hipSuccess;
     const int64_t waves = (a.sch.n_hub + a.geo.G - 1) / a.geo.G;
     const dim3 grid(blocks_for_waves(waves)), block(WAVE * WPB);
-    if (a.geo.ov) return launch_spmm_combine_ov(a, dtype, maxmin, grid, block, s);
+    if (a.geo.ov) return launch_spmm_combine_ov(a, dtype, grid, block, s);  // (sums)
     if (dtype == 0) {
-        GNNK_VEC_DISPATCH_F32(vec, launch_combine_t<float, V, false>(a, maxmin, grid, block, s))
+        GNNK_VEC_DISPATCH_F32(vec, launch_combine_t<float, V>(a, maxmin, grid, block, s))
     } else {
-        GNNK_VEC_DISPATCH_BF16(vec, launch_combine_t<bf16_t, V, false>(a, maxmin, grid, block, s))
+        GNNK_VEC_DISPATCH_BF16(vec, launch_combine_t<bf16_t, V>(a, maxmin, grid, block, s))
     }
     return hipGetLastError();
 }

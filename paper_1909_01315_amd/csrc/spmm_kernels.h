@@ -405,7 +405,7 @@ __global__ __launch_bounds__(256) void spmm_cmp_kernel(EngineArgs A) {
     }
 }
 
-template <typename T, int VEC, bool OV>
+template <typename T, int VEC>
 __global__ __launch_bounds__(256) void spmm_cmp_combine_kernel(EngineArgs A) {
     const int w = wave_id();
     const GeomDev& geo = A.geo;
@@ -421,7 +421,7 @@ __global__ __launch_bounds__(256) void spmm_cmp_combine_kernel(EngineArgs A) {
     for (int ch = 0; ch < geo.nchunk; ++ch) {
         const int j = ch * geo.L + ln.lig;
         const bool active = j < geo.NV && row_ok;
-        const int col0 = cols_of<VEC, OV>(geo, active, j).col0;
+        const int col0 = cols_of<VEC, false>(geo, active, j).col0;
         float best[VEC];
         int32_t be[VEC], bn[VEC];
 #pragma unroll
@@ -526,10 +526,10 @@ void launch_cmp_ov(const EngineArgs& a, int opk, int spec, int gc, dim3 grid, di
     GNNK_OPK_DISPATCH(opk, { hipLaunchKernelGGL((spmm_cmp_kernel<T, V, K, SpecDynT<OV>>), grid, block, 0, s, a); })
 }
 
-template <typename T, int V, bool OV>
+template <typename T, int V>
 void launch_combine_t(const EngineArgs& a, bool maxmin, dim3 grid, dim3 block, hipStream_t s) {
-    if (maxmin) hipLaunchKernelGGL((spmm_cmp_combine_kernel<T, V, OV>), grid, block, 0, s, a);
-    else hipLaunchKernelGGL((spmm_sum_combine_kernel<T, V, OV>), grid, block, 0, s, a);
+    if (maxmin) hipLaunchKernelGGL((spmm_cmp_combine_kernel<T, V>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((spmm_sum_combine_kernel<T, V, false>), grid, block, 0, s, a);
 }
 
 }  // namespace gnnk

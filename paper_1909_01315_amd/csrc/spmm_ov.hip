@@ -17,9 +17,10 @@ hipError_t launch_spmm_ov(const EngineArgs& a, int dtype, bool maxmin, int opk, 
     return hipGetLastError();
 }
 
-hipError_t launch_spmm_combine_ov(const EngineArgs& a, int dtype, bool maxmin, dim3 grid, dim3 block, hipStream_t s) {
-    if (dtype == 0) launch_combine_t<float, 4, true>(a, maxmin, grid, block, s);
-    else launch_combine_t<bf16_t, 8, true>(a, maxmin, grid, block, s);
+// (max and min combine with exact vectors)
+hipError_t launch_spmm_combine_ov(const EngineArgs& a, int dtype, dim3 grid, dim3 block, hipStream_t s) {
+    if (dtype == 0) hipLaunchKernelGGL((spmm_sum_combine_kernel<float, 4, true>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((spmm_sum_combine_kernel<bf16_t, 8, true>), grid, block, 0, s, a);
     return hipGetLastError();
 }
 

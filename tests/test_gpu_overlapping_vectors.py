@@ -50,7 +50,9 @@ def shifted(a, pad):
 
 
 WIDTHS = [(1, 5, 0), (1, 7, 0), (1, 9, 0), (1, 15, 1), (1, 33, 0), (1, 35, 0), (1, 39, 3), (1, 47, 0), (1, 64, 1),
-          (1, 261, 0), (1, 515, 0), (3, 5, 0), (3, 9, 1), (2, 45, 0), (7, 13, 0)]
+          (1, 261, 0), (1, 515, 0), (3, 5, 0), (3, 9, 1), (2, 45, 0), (7, 13, 0),
+          # the narrowest rows that overlap, and the widest that do not
+          (1, 13, 0), (1, 14, 0), (1, 17, 0), (1, 18, 1), (2, 5, 0), (2, 9, 0), (4, 5, 0), (3, 6, 0)]
 
 
 @pytest.mark.parametrize("no_fast", [0, 1])
