@@ -120,8 +120,17 @@ __device__ __forceinline__ float gat_score(float el, float er, float slope) {
     return s > 0.0f ? s : slope * s;
 }
 
-// consumer of a row's edges: a full batch at once, others one by one
-template <typename T, int VEC>
+// consumer of a row's edges: a full batch at once, others one by one.
+// BATCHED = false: the runtime layouts of one or two columns a lane, which have
+// no full batches.  Edge by edge the state of some lane of a wavefront nearly
+// always grows, and add() then takes two exponentials an edge where add_any()
+// takes one: bf16, 8 heads of 5 columns, 1M and 8.4M edges, 73 -> 67 and
+// 528 -> 501 us.  Those of four or more columns, a whole row in a lane each,
+// keep add(): 8.4M edges, fp32, 4 columns, 100 us with it, 107 without.
+template <int VEC, class S>
+constexpr bool gat_batched = S::FAST || VEC >= 4;
+
+template <typename T, int VEC, bool BATCHED>
 struct GatSink {
     Online<VEC>& st;
     float er_h, slope;
@@ -133,10 +142,14 @@ struct GatSink {
         st.template add<UNR>(s, [&](int u) { return rw[u].a; });
     }
     __device__ __forceinline__ void operator()(const Raw<VEC>& rw, int32_t, int32_t, bool ok) {
-        // a slot outside the row holds another edge's values and scores -inf:
-        // it weighs nothing (0 times an infinite value: see gat_again)
-        const float s = ok ? gat_score<T>(rw.b[0], er_h, slope) : -INFINITY;
-        st.template add<1>(&s, [&](int) { return rw.a; });
+        if constexpr (!BATCHED) {
+            if (ok) st.add_any(gat_score<T>(rw.b[0], er_h, slope), rw.a);
+        } else {
+            // a slot outside the row holds another edge's values and scores
+            // -inf: it weighs nothing (0 times an infinite value: see gat_again)
+            const float s = ok ? gat_score<T>(rw.b[0], er_h, slope) : -INFINITY;
+            st.template add<1>(&s, [&](int) { return rw.a; });
+        }
     }
 };
 
@@ -226,9 +239,10 @@ __global__ __launch_bounds__(256) void gat_kernel(EngineArgs A, GatArgs G) {
             Online<VEC> st;
             st.init();
             Pre<VEC> pre;
-            GatSink<T, VEC> sink{st, er_h, G.slope};
+            GatSink<T, VEC, gat_batched<VEC, S>> sink{st, er_h, G.slope};
             walk_row<T, VEC, 1, EXT_NONE, S>(A, (int32_t)r, b, e, ln.g, Gn, col0, h, pre, sink);
-            gat_again<T, VEC>(A, (int32_t)b, (int32_t)e, ln.g, Gn, col0, h, er_h, G.slope, st);
+            if constexpr (gat_batched<VEC, S>)
+                gat_again<T, VEC>(A, (int32_t)b, (int32_t)e, ln.g, Gn, col0, h, er_h, G.slope, st);
             for (int s = L; s < WAVE; s <<= 1) {
                 double oacc[VEC];
 #pragma unroll
@@ -274,9 +288,10 @@ __global__ __launch_bounds__(256) void gat_kernel(EngineArgs A, GatArgs G) {
             Online<VEC> st;
             st.init();
             Pre<VEC> pre;
-            GatSink<T, VEC> sink{st, er_h, G.slope};
+            GatSink<T, VEC, gat_batched<VEC, S>> sink{st, er_h, G.slope};
             walk_lane<T, VEC, 1, EXT_NONE, S>(A, self, b, e, col0, h, pre, sink);
-            gat_again<T, VEC>(A, (int32_t)b, (int32_t)e, 0, 1, col0, h, er_h, G.slope, st);
+            if constexpr (gat_batched<VEC, S>)
+                gat_again<T, VEC>(A, (int32_t)b, (int32_t)e, 0, 1, col0, h, er_h, G.slope, st);
             if (r >= 0 && active) {
                 float v[VEC];
 #pragma unroll
